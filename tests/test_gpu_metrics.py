@@ -47,3 +47,16 @@ def test_metrics_special_cases_and_per_env_start():
     want = np.stack([backtest_metrics(r[:, :1], 1024.0, 2.0 ** -12)[0], backtest_metrics(r[:, 1:], 4096.0, 2.0 ** -12)[0]])
     assert _close(got, want).all()
     assert got[0, 3] == np.inf and got[0, 4] == 0.0
+
+
+@pytest.mark.parametrize("N,T", [(1, 1), (8, 256), (9, 257), (23, 700)])
+def test_metrics_at_pass_and_tile_edges(N, T):
+    """Days around whole passes (256) and environments around whole workgroups (8)."""
+    import torch
+    from paper_2501_10709_amd import binding as B
+    dev = cuda()
+    r = np.random.default_rng(7).normal(0.1, 2.0, (T, N))
+    r[:, 0] = np.abs(r[:, 0])  # no losses: the ratios over them are infinite
+    got = B.fm_backtest_metrics(torch.from_numpy(r).to(dev), 1e6, 2.0 ** -12).cpu().numpy()
+    want = backtest_metrics(r, 1e6, 2.0 ** -12)
+    assert _close(got, want).all(), (got, want)
