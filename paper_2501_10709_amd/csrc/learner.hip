@@ -22,149 +22,316 @@
 namespace fm {
 namespace lrn {
 
-constexpr int kTile = 128, kBK = 16, kThreads = 256, kMaxK = 8;
+constexpr int kMaxK = 8;
+constexpr int kBK = 32, kThreads = 512, kWaves = kThreads / 64;
 
 enum Epilogue { kBiasTanh = 0, kMaskTanhGrad = 1, kStore = 2 };
 
-// C(m, n) = sum_k A(m, k) B(k, n) over k in the block's range, with element (m, k) of A at
-// A[m * sam + k * sak] and (k, n) of B at B[k * sbk + n * sbn].  blockIdx.z selects a chunk of
-// kc values of k (split reductions) and offsets C by z * scz.  Epilogues: kBiasTanh,
-// C = tanh(acc + bias[n]) (from one exp2 and one reciprocal, absolute error below 1e-6); kMaskTanhGrad, C = acc * (1 - X^2) with X at the same place as C (C may
-// be X itself: each element is read and written by one thread); kStore, C = acc.  A workgroup
-// computes a 128 x TN tile: for TN = 128 each of its four wavefronts a 64 x 64 quarter, for
-// TN = 32 (outputs at most 32 wide) a 32 x 32 quarter of the rows, as blocks of float32 MFMAs
-// (16 x 16 x 4), accumulating over k in ascending order of 4-element steps.  The tile width
-// changes only which threads compute an element, not its arithmetic.
+// C(m, n) = sum_k A(m, k) B(k, n) over k in the block's range; C is [M][ldc].  A chunk of kc values
+// of k (split reductions) offsets C by chunk * scz.  The epilogue fixes the operands' layouts:
+//   kBiasTanh      A [M][lda], B [K][ldb]: C = tanh(acc + bias[n]) (from one exp2 and one
+//                  reciprocal, absolute error below 1e-6);
+//   kMaskTanhGrad  A [M][lda], B [N][ldb]: C = acc * (1 - X^2) with X at the same place as C (C may
+//                  be X itself: each element is read and written by one thread);
+//   kStore         A [K][lda], B [K][ldb]: C = acc.
 struct Gemm {
   const float* A;
-  long sam, sak;
   const float* B;
-  long sbk, sbn;
   float* C;
-  long scm, scn, scz;
   const float* bias;
   const float* X;
-  int M, N, K, kc;
-  int ones_row;  // rows m >= ones_row of A read as 1 (appends the column sums of B: bias gradients)
-  // colsum: the workgroups of row tile 0 also sum B's columns over their k range (ascending k,
-  // float32) and store them as row bias_row of C -- the column sums without a row tile of their
-  // own when M is a multiple of the tile height.
-  int colsum, bias_row;
+  int lda, ldb, ldc;
+  long scz;
+  int M, N, K, kc, chunks;
+  // kStore (bias gradients): C has a row ones_row with the column sums of B.  With ONES, rows
+  // m >= ones_row of A (inside M) read as 1; else the workgroups of row tile 0 sum B's columns over
+  // their k range (float32), without a row tile for that row when ones_row fills whole tiles.
+  int ones_row;
 };
 
-template <int EPI, int TN>
+// Float32 products on the bfloat16 matrix cores.  Every float32 x is the exact sum of three
+// bfloat16 values, hi = bf16(x), mid = bf16(x - hi), lo = x - hi - mid (24 bits in three times 8),
+// and x y is the sum of nine products, of which mid*lo, lo*mid and lo*lo are below 2^-25 |x y| and
+// left out.  The other six take 6 x 16 cycles of a SIMD's matrix core for a 16 x 16 x 32 block,
+// where v_mfma_f32_16x16x4 takes 8 x 32.  The matrix core rounds a
+// sum that starts from zero to nearest, but adds a non-zero accumulator with its lower bits cut
+// off, towards minus infinity: a bias that is the same in every row and adds up over a gradient
+// (seven times the float32 form's error).  So 32 terms of hi*hi are summed from zero, those of the
+// five small products in a chain of their own (where what is cut off is 2^-8 of that), and both
+// are added to the running float32 sum by ordinary additions.  An
+// operand that is infinite, NaN or beyond the bfloat16 range makes a sum NaN (hi is infinite and
+// x - hi has no value); a wavefront that finds one sums its elements again in float32.
+__device__ __forceinline__ void split2(float x0, float x1, unsigned (&p)[3]) {
+  typedef float f2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+  const auto pk = [](float a, float b) { return __builtin_bit_cast(unsigned, __builtin_convertvector(f2{a, b}, b2)); };
+  const auto lo_of = [](unsigned v) { return __uint_as_float(v << 16); };
+  const auto hi_of = [](unsigned v) { return __uint_as_float(v & 0xffff0000u); };
+  p[2] = pk(x0, x1);
+  const float r0 = x0 - lo_of(p[2]), r1 = x1 - hi_of(p[2]);
+  p[1] = pk(r0, r1);
+  p[0] = pk(r0 - lo_of(p[1]), r1 - hi_of(p[1]));
+}
+
+// An operand tile of R rows (m or n) by kBK k in LDS: three planes (lo, mid, hi) of MFMA fragments
+// [R / 16][64 lanes][8], lane 16 kg + r of a fragment holding row r, k 8 kg .. 8 kg + 7, with r
+// XORed by 4 kg so that neither the fragment reads nor the writes of either load order conflict.
+// KF: the matrix has k as its unit-stride index ([rows][ld]), else the rows ([K][ld]).  The loads
+// go through a buffer resource over the block's rows or k, moved along k, with 32-bit offsets that
+// do not change; what lies beyond reads as zero.
+template <int R, bool KF>
+struct Operand {
+  static constexpr int kItems = (R * 4 + kThreads - 1) / kThreads;  // (row, 8 k) units per thread
+  static constexpr int kPlane = R * kBK;                            // elements per plane
+  static constexpr unsigned kBeyond = 0x7ffffff0;
+  float x[kItems][8];
+
+  // Item e of this thread: row r and k group kg; walks the unit-stride index across threads.
+  static __device__ __forceinline__ bool at(int e, int& r, int& kg) {
+    const int q = threadIdx.x + kThreads * e;
+    r = KF ? q >> 2 : q % R;
+    kg = KF ? q & 3 : q / R;
+    return q < 4 * R;
+  }
+  // Requests item e of the block of rows r0 .. and k0 .. (k < k_end).
+  __device__ __forceinline__ void fetch(int e, const float* p, int ld, int r0, int rows, int k0, int k_end) {
+    const int nr = min(R, rows - r0), nk = min(kBK, k_end - k0);
+    const float* base = KF ? p + static_cast<long>(r0) * ld + k0 : p + static_cast<long>(k0) * ld + r0;
+    const int bytes = 4 * (KF ? nr * ld - k0 : nk * ld - r0);
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, bytes, 0x00020000);
+    int r, kg;
+    const bool mine = at(e, r, kg);
+    if constexpr (KF) {
+      const unsigned o = mine ? 4u * (r * ld + 8 * kg) : kBeyond;
+      if (nk == kBK) {
+        const auto u = __builtin_amdgcn_raw_buffer_load_b128(rs, o, 0, 0);
+        const auto v = __builtin_amdgcn_raw_buffer_load_b128(rs, o + 16, 0, 0);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          x[e][j] = __uint_as_float(u[j]);
+          x[e][4 + j] = __uint_as_float(v[j]);
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          x[e][j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, 8 * kg + j < nk ? o + 4 * j : kBeyond, 0, 0));
+      }
+    } else {
+      const unsigned o = mine && r < nr ? 4u * (8 * kg * ld + r) : kBeyond;
+      // One resource per k, so that the offset is the same register for all eight.
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const __amdgpu_buffer_rsrc_t rj = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float*>(base) + static_cast<long>(j) * ld, 0, max(bytes - 4 * j * ld, 0), 0x00020000);
+        x[e][j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rj, o, 0, 0));
+      }
+    }
+  }
+  // Rows first .. rows - 1 of item e read as one (for k < k_end).
+  __device__ __forceinline__ void ones(int e, int first, int rows, int r0, int k0, int k_end) {
+    int r, kg;
+    (void)at(e, r, kg);
+    const bool one = r0 + r >= first && r0 + r < rows;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[e][j] = one && k0 + 8 * kg + j < k_end ? 1.0f : x[e][j];
+  }
+  typedef unsigned u4 __attribute__((ext_vector_type(4)));
+  // Elements 2 j and 2 j + 1 of item e into the planes' registers.
+  __device__ __forceinline__ void split(int e, int j, u4 (&pl)[3]) const {
+    unsigned p[3];
+    split2(x[e][2 * j], x[e][2 * j + 1], p);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) pl[q][j] = p[q];
+  }
+  static __device__ __forceinline__ void store(int e, __bf16* lds, const u4 (&pl)[3]) {
+    int r, kg;
+    if (!at(e, r, kg)) return;
+    const int o = (r / 16 * 64 + 16 * kg + ((r & 15) ^ (4 * kg))) * 8;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) *reinterpret_cast<u4*>(lds + q * kPlane + o) = pl[q];
+  }
+  static __device__ __forceinline__ bf16x8 frag(const __bf16* lds, int plane, int block, int lane) {
+    const int kg = lane >> 4;
+    return *reinterpret_cast<const bf16x8*>(lds + plane * kPlane + (block * 64 + 16 * kg + ((lane & 15) ^ (4 * kg))) * 8);
+  }
+};
+
+// A TM x TN tile of C per workgroup, eight wavefronts of BI x BJ blocks each.  Bound by instruction
+// issue: a wavefront's 24 products per (block column, 32 k) leave room for about three vector
+// instructions each, and the split (5.5 an element) and the sums (2 an element and 32 k) take most
+// of it.  One workgroup per compute unit (two wavefronts per SIMD), the operand tiles
+// double-buffered in LDS: while block k is multiplied, block k + 1 is split into the other buffer
+// from registers and block k + 2 is requested.  Tiles are 256 wide where C is (every row of A is
+// then read and split once), and as narrow as C's width otherwise.
+template <int EPI, int TM, int TN, bool ONES>
 __global__ __launch_bounds__(kThreads) void gemm_kernel(Gemm g) {
-  static_assert(TN == kTile || TN == 32, "tiles 128 x 128 or 128 x 32");
-  // Wavefronts along n (WN) and m; each owns BI x BJ blocks of 16 x 16.
-  constexpr int WN = TN == kTile ? 2 : 1, BI = kTile / (4 / WN) / 16, BJ = TN / WN / 16;
-  // Rows padded by 16 floats: the two k rows a half-wavefront reads sit 16 banks apart.
-  __shared__ float As[kBK][kTile + 16];
-  __shared__ float Bs[kBK][TN + 16];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int m0 = blockIdx.x * kTile, n0 = blockIdx.y * TN;
-  const int wm = (wave / WN) * 16 * BI, wn = (wave % WN) * 16 * BJ;  // this wavefront's quarter
+  constexpr int WN = TN >= 128 ? TN / 64 : 1, WM = kWaves / WN;  // wavefronts along n and m
+  constexpr int BI = TM / WM / 16, BJ = TN / WN / 16;
+  using OpA = Operand<TM, EPI != kStore>;
+  using OpB = Operand<TN, EPI == kMaskTanhGrad>;
+  using u4 = typename OpA::u4;
+  constexpr bool kColsum = EPI == kStore && !ONES;
+  extern __shared__ __align__(16) __bf16 lds[];
+  constexpr int kBuf = 3 * (OpA::kPlane + OpB::kPlane);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int bm = (wave / WN) * BI, bn = (wave % WN) * BJ;  // this wavefront's first blocks
+  const int m0 = blockIdx.x * TM, n0 = blockIdx.y * TN;
   const int k_begin = blockIdx.z * g.kc, k_end = min(g.K, k_begin + g.kc);
-  // Loads walk the operand's unit-stride index across neighbouring threads (coalesced).  Thread
-  // tid moves elements e = 0..kPerA-1 of A's k-block (am, ak) and 0..kPerB-1 of B's (bk, bn).
-  constexpr int kPerA = kTile * kBK / kThreads, kPerB = TN * kBK / kThreads;
-  const bool a_kfast = g.sak == 1, b_kfast = g.sbk == 1;
-  const int am0 = a_kfast ? tid / kBK : tid % kTile, ak0 = a_kfast ? tid % kBK : tid / kTile;
-  const int bn0 = b_kfast ? tid / kBK : tid % TN, bk0 = b_kfast ? tid % kBK : tid / TN;
-  constexpr int kStepFast = kThreads / kBK, kStepSlowA = kThreads / kTile, kStepSlowB = kThreads / TN;
-  auto a_at = [&](int e, int& am, int& ak) {
-    am = a_kfast ? am0 + kStepFast * e : am0;
-    ak = a_kfast ? ak0 : ak0 + kStepSlowA * e;
-  };
-  auto b_at = [&](int e, int& bk, int& bn) {
-    bn = b_kfast ? bn0 + kStepFast * e : bn0;
-    bk = b_kfast ? bk0 : bk0 + kStepSlowB * e;
-  };
-  // The next k-block is read into registers while the current one is multiplied.
-  float ra[kPerA], rb[kPerB];
-  auto fetch = [&](int k0) {
+  OpA a;
+  OpB b;
+  const auto fetch = [&](int k0) {
 #pragma unroll
-    for (int e = 0; e < kPerA; ++e) {
-      int am, ak;
-      a_at(e, am, ak);
-      const int m = m0 + am, k = k0 + ak;
-      ra[e] = (m < g.M && k < k_end) ? (m < g.ones_row ? g.A[m * g.sam + k * g.sak] : 1.0f) : 0.0f;
+    for (int e = 0; e < OpA::kItems; ++e) a.fetch(e, g.A, g.lda, m0, min(g.M, g.ones_row), k0, k_end);
+#pragma unroll
+    for (int e = 0; e < OpB::kItems; ++e) b.fetch(e, g.B, g.ldb, n0, g.N, k0, k_end);
+  };
+  // Column sums of B: a thread's items are always the same columns.
+  float csum[OpB::kItems];
+#pragma unroll
+  for (int e = 0; e < OpB::kItems; ++e) csum[e] = 0.0f;
+  const auto commit = [&](int buf, int k0) {
+    __bf16* l = lds + buf * kBuf;
+#pragma unroll
+    for (int e = 0; e < OpA::kItems; ++e) {
+      if (ONES) a.ones(e, g.ones_row, g.M, m0, k0, k_end);
+      u4 pl[3];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) a.split(e, j, pl);
+      OpA::store(e, l, pl);
     }
 #pragma unroll
-    for (int e = 0; e < kPerB; ++e) {
-      int bk, bn;
-      b_at(e, bk, bn);
-      const int n = n0 + bn, kb = k0 + bk;
-      rb[e] = (n < g.N && kb < k_end) ? g.B[kb * g.sbk + n * g.sbn] : 0.0f;
+    for (int e = 0; e < OpB::kItems; ++e) {
+      u4 pl[3];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        b.split(e, j, pl);
+        if (kColsum) csum[e] = (csum[e] + b.x[e][2 * j]) + b.x[e][2 * j + 1];
+      }
+      OpB::store(e, l + 3 * OpA::kPlane, pl);
     }
   };
+  constexpr floatx4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
   floatx4 acc[BI][BJ];
 #pragma unroll
   for (int i = 0; i < BI; ++i)
 #pragma unroll
-    for (int j = 0; j < BJ; ++j) acc[i][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-  const bool do_colsum = g.colsum && blockIdx.x == 0 && tid < TN;
-  float csum = 0.0f;
-  if (k_begin < k_end) fetch(k_begin);
-  for (int k0 = k_begin; k0 < k_end; k0 += kBK) {
-#pragma unroll
-    for (int e = 0; e < kPerA; ++e) {
-      int am, ak;
-      a_at(e, am, ak);
-      As[ak][am] = ra[e];
+    for (int j = 0; j < BJ; ++j) acc[i][j] = zero;
+  if (k_begin < k_end) {
+    fetch(k_begin);
+    commit(0, k_begin);
+    if (k_begin + kBK < k_end) fetch(k_begin + kBK);
+  }
+  __syncthreads();
+  int buf = 0;
+  for (int k0 = k_begin; k0 < k_end; k0 += kBK, buf ^= 1) {
+    if (k0 + kBK < k_end) {
+      commit(buf ^ 1, k0 + kBK);
+      if (k0 + 2 * kBK < k_end) fetch(k0 + 2 * kBK);
     }
+    const __bf16* la = lds + buf * kBuf;
+    const __bf16* lb = la + 3 * OpA::kPlane;
+    bf16x8 fa[BI][3];
 #pragma unroll
-    for (int e = 0; e < kPerB; ++e) {
-      int bk, bn;
-      b_at(e, bk, bn);
-      Bs[bk][bn] = rb[e];
-    }
-    __syncthreads();
-    if (k0 + kBK < k_end) fetch(k0 + kBK);
-    if (do_colsum) {
-      // Rows beyond k_end were stored as zero, so they add nothing.
+    for (int i = 0; i < BI; ++i)
 #pragma unroll
-      for (int kk = 0; kk < kBK; ++kk) csum = csum + Bs[kk][tid];
-    }
-    // v_mfma_f32_16x16x4_f32: lane l supplies A[row l%16][k l/16] and B[k l/16][col l%16].
+      for (int p = 0; p < 3; ++p) fa[i][p] = OpA::frag(la, p, bm + i, lane);
 #pragma unroll
-    for (int kq = 0; kq < kBK; kq += 4) {
-      float a[BI], b[BJ];
+    for (int j = 0; j < BJ; ++j) {
+      bf16x8 fb[3];
 #pragma unroll
-      for (int i = 0; i < BI; ++i) a[i] = As[kq + (lane >> 4)][wm + 16 * i + (lane & 15)];
+      for (int p = 0; p < 3; ++p) fb[p] = OpB::frag(lb, p, bn + j, lane);
+      // Products (plane of A, plane of B): hi*hi, then the five small ones; BI independent sums
+      // between dependent products.
+      constexpr int PA[6] = {2, 0, 1, 2, 1, 2}, PB[6] = {2, 2, 1, 0, 2, 1};
+      floatx4 big[BI], small[BI];
 #pragma unroll
-      for (int j = 0; j < BJ; ++j) b[j] = Bs[kq + (lane >> 4)][wn + 16 * j + (lane & 15)];
+      for (int q = 0; q < 6; ++q)
+#pragma unroll
+        for (int i = 0; i < BI; ++i) {
+          floatx4& t = q == 0 ? big[i] : small[i];
+          t = mfma_bf16(fa[i][PA[q]], fb[PB[q]], q < 2 ? zero : t);
+        }
 #pragma unroll
       for (int i = 0; i < BI; ++i)
 #pragma unroll
-        for (int j = 0; j < BJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
+        for (int r = 0; r < 4; ++r) acc[i][j][r] = acc[i][j][r] + (big[i][r] + small[i][r]);
     }
     __syncthreads();
   }
-  // Lane l holds column l%16 and rows 4(l/16)..4(l/16)+3 of each 16 x 16 block.
-  float* C = g.C + blockIdx.z * g.scz;
-  if (do_colsum && n0 + tid < g.N) C[static_cast<long>(g.bias_row) * g.scm + (n0 + tid) * g.scn] = csum;
+  float* Cz = g.C + blockIdx.z * g.scz;
+  if (kColsum && m0 == 0) {
+    // The partial column sums of the threads that share a column, in thread order.
+    float* sums = reinterpret_cast<float*>(lds);
+#pragma unroll
+    for (int e = 0; e < OpB::kItems; ++e)
+      if (tid + kThreads * e < 4 * TN) sums[tid + kThreads * e] = csum[e];
+    __syncthreads();
+    if (tid < TN && n0 + tid < g.N)
+      Cz[static_cast<long>(g.ones_row) * g.ldc + n0 + tid] =
+          ((sums[tid] + sums[TN + tid]) + sums[2 * TN + tid]) + sums[3 * TN + tid];
+  }
+  // Lane l holds column l%16 and rows 4(l/16)..4(l/16)+3 of each 16 x 16 block.  Offsets in
+  // bytes from the tile's first element, through a resource over the tile's rows; derived from
+  // an opaque copy of the lane so that they are not kept in registers over the loop.
+  int le = lane;
+  asm volatile("" : "+v"(le));
+  const int mb = 16 * bm + 4 * (le >> 4), nb = 16 * bn + (le & 15);
+  const int mr = min(TM, g.M - m0), nr = g.N - n0;  // rows and columns of this tile
+  const long first = static_cast<long>(m0) * g.ldc + n0;
+  const int bytes = 4 * (mr * g.ldc - n0);
+  const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(Cz + first, 0, bytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float*>(EPI == kMaskTanhGrad ? g.X + first : Cz + first), 0, bytes, 0x00020000);
+  const auto mask = [&](unsigned o) {
+    return EPI == kMaskTanhGrad ? __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rx, o, 0, 0)) : 0.0f;
+  };
+  const auto put = [&](unsigned o, float v, float bias, float x) {
+    if (EPI == kBiasTanh) v = fast_tanh(v + bias);
+    if (EPI == kMaskTanhGrad) v = v * (1.0f - x * x);
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rc, o, 0, 0);
+  };
+  bool nan = false;
 #pragma unroll
   for (int i = 0; i < BI; ++i)
 #pragma unroll
-    for (int j = 0; j < BJ; ++j) {
-      const int n = n0 + wn + 16 * j + (lane & 15);
-      if (n >= g.N) continue;
+    for (int j = 0; j < BJ; ++j)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = m0 + wm + 16 * i + 4 * (lane >> 4) + r;
-        if (m >= g.M) continue;
-        const long o = m * g.scm + n * g.scn;
-        const float v = acc[i][j][r];
-        if (EPI == kBiasTanh) {
-          C[o] = fast_tanh(v + g.bias[n]);
-        } else if (EPI == kMaskTanhGrad) {
-          const float x = g.X[o];
-          C[o] = v * (1.0f - x * x);
-        } else {
-          C[o] = v;
-        }
-      }
+      for (int r = 0; r < 4; ++r) nan = nan || acc[i][j][r] != acc[i][j][r];
+  if (__builtin_amdgcn_ballot_w64(nan) == 0) {
+#pragma unroll
+    for (int j = 0; j < BJ; ++j) {
+      const int n = nb + 16 * j;
+      const bool on = n < nr;
+      const float bias = EPI == kBiasTanh && on ? g.bias[n0 + n] : 0.0f;
+      const unsigned o = on ? 4u * (mb * g.ldc + n) : OpA::kBeyond;
+      // A column's masks are all requested before its first store (which they cannot pass).
+      float x[BI][4];
+#pragma unroll
+      for (int i = 0; i < BI; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[i][r] = mask(o + 4u * (16 * i + r) * g.ldc);
+#pragma unroll
+      for (int i = 0; i < BI; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) put(o + 4u * (16 * i + r) * g.ldc, acc[i][j][r], bias, x[i][r]);
     }
+  } else {
+#pragma unroll 1
+    for (int e = 0; e < 4 * BI * BJ; ++e) {
+      const int m = mb + 16 * (e / (4 * BJ)) + e % 4, n = nb + 16 * (e / 4 % BJ);
+      if (m >= mr || n >= nr) continue;
+      float v = 0.0f;
+      for (int k = k_begin; k < k_end; ++k) {
+        const float av = EPI == kStore ? (m0 + m < g.ones_row ? g.A[static_cast<long>(k) * g.lda + m0 + m] : 1.0f)
+                                       : g.A[static_cast<long>(m0 + m) * g.lda + k];
+        const float bv = EPI == kMaskTanhGrad ? g.B[static_cast<long>(n0 + n) * g.ldb + k]
+                                              : g.B[static_cast<long>(k) * g.ldb + n0 + n];
+        v = fmaf(av, bv, v);
+      }
+      const unsigned o = 4u * (m * g.ldc + n);
+      put(o, v, EPI == kBiasTanh ? g.bias[n0 + n] : 0.0f, mask(o));
+    }
+  }
 }
 
 // R_n = sum_t r[t][n] in ascending t.
@@ -257,17 +424,28 @@ Layout layout(int K, int S, int H, int A, int N, int T) {
   return L;
 }
 
-// Outputs at most 32 wide (the action layer) take 128 x 32 tiles instead of padding to 128.
-template <int EPI>
-hipError_t gemm(const Gemm& g, int z, hipStream_t stream) {
-  if (g.N <= 32) {
-    const dim3 grid((g.M + kTile - 1) / kTile, 1, z);
-    hipLaunchKernelGGL((gemm_kernel<EPI, 32>), grid, dim3(kThreads), 0, stream, g);
-  } else {
-    const dim3 grid((g.M + kTile - 1) / kTile, (g.N + kTile - 1) / kTile, z);
-    hipLaunchKernelGGL((gemm_kernel<EPI, kTile>), grid, dim3(kThreads), 0, stream, g);
-  }
+// Rows of A that a workgroup takes for C's width (its tile width is the width rounded up to 32,
+// 64, 128 or 256).
+constexpr int tile_rows(int N) { return N <= 128 ? 256 : 128; }
+
+template <int EPI, int TN, bool ONES>
+hipError_t gemm_tiles(const Gemm& g, hipStream_t stream) {
+  constexpr int TM = tile_rows(TN);
+  constexpr size_t lds = 2 * 3 * sizeof(__bf16) * kBK * (TM + TN);
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_kernel<EPI, TM, TN, ONES>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+  if (e != hipSuccess) return e;
+  const dim3 grid((g.M + TM - 1) / TM, (g.N + TN - 1) / TN, g.chunks);
+  hipLaunchKernelGGL((gemm_kernel<EPI, TM, TN, ONES>), grid, dim3(kThreads), lds, stream, g);
   return hipGetLastError();
+}
+
+template <int EPI, bool ONES = false>
+hipError_t gemm(const Gemm& g, hipStream_t stream) {
+  if (g.N <= 32) return gemm_tiles<EPI, 32, ONES>(g, stream);
+  if (g.N <= 64) return gemm_tiles<EPI, 64, ONES>(g, stream);
+  if (g.N <= 128) return gemm_tiles<EPI, 128, ONES>(g, stream);
+  return gemm_tiles<EPI, 256, ONES>(g, stream);
 }
 
 // Weight and bias gradients [X | 1]^T G: Xr [rows][kin] (row stride ldx), Gr [rows][kout]; the
@@ -277,26 +455,22 @@ hipError_t weight_grad(const Layout& L, const float* Xr, int kin, int ldx, const
                        float* out, hipStream_t stream) {
   Gemm g{};
   g.A = Xr;
-  g.sam = 1;
-  g.sak = ldx;
+  g.lda = ldx;
   g.B = Gr;
-  g.sbk = kout;
-  g.sbn = 1;
+  g.ldb = kout;
   g.C = P;
-  g.scm = kout;
-  g.scn = 1;
+  g.ldc = kout;
   g.scz = static_cast<long>(kin + 1) * kout;
   // With kin a multiple of the tile height the bias row (the column sums of G) would take a row
   // tile of its own; the first row tile's workgroups sum the columns instead.
-  const bool own = kin % kTile == 0;
+  const bool own = kin % tile_rows(kout) == 0;
   g.M = own ? kin : kin + 1;
   g.N = kout;
   g.K = L.rows;
   g.kc = L.chunk;
+  g.chunks = L.n_chunks;
   g.ones_row = kin;
-  g.colsum = own ? 1 : 0;
-  g.bias_row = kin;
-  hipError_t e = gemm<kStore>(g, L.n_chunks, stream);
+  hipError_t e = own ? gemm<kStore>(g, stream) : gemm<kStore, true>(g, stream);
   if (e != hipSuccess) return e;
   const int len = (kin + 1) * kout;
   hipLaunchKernelGGL(reduce_kernel, dim3((len + 255) / 256), dim3(256), 0, stream, P, len, L.n_chunks, out);
@@ -309,21 +483,19 @@ hipError_t back_delta(const Layout& L, const float* Gin, int kout, const float* 
                       hipStream_t stream) {
   Gemm g{};
   g.A = Gin;
-  g.sam = kout;
-  g.sak = 1;
+  g.lda = kout;
   g.B = W;
-  g.sbk = 1;
-  g.sbn = kout;
+  g.ldb = kout;
   g.C = X;
-  g.scm = kin;
-  g.scn = 1;
+  g.ldc = kin;
   g.X = X;
   g.M = L.rows;
   g.N = kin;
   g.K = kout;
   g.kc = kout;
+  g.chunks = 1;
   g.ones_row = g.M;
-  return gemm<kMaskTanhGrad>(g, 1, stream);
+  return gemm<kMaskTanhGrad>(g, stream);
 }
 
 // Y [rows][kout] = tanh(X [rows][kin] W + b).
@@ -331,21 +503,19 @@ hipError_t layer(const Layout& L, const float* X, int kin, const float* W, const
                  hipStream_t stream) {
   Gemm g{};
   g.A = X;
-  g.sam = kin;
-  g.sak = 1;
+  g.lda = kin;
   g.B = W;
-  g.sbk = kout;
-  g.sbn = 1;
+  g.ldb = kout;
   g.C = Y;
-  g.scm = kout;
-  g.scn = 1;
+  g.ldc = kout;
   g.bias = b;
   g.M = L.rows;
   g.N = kout;
   g.K = kin;
   g.kc = kin;
+  g.chunks = 1;
   g.ones_row = g.M;
-  return gemm<kBiasTanh>(g, 1, stream);
+  return gemm<kBiasTanh>(g, stream);
 }
 
 bool dims_ok(int K, int S, int H, int A, int N, int T) {

@@ -98,3 +98,69 @@ def test_policy_gradient_argument_errors():
     small = torch.empty(256, dtype=torch.uint8, device="cuda")
     with pytest.raises(B.FmError):
         B.fm_policy_gradient(K, S, H, A, w, 0, st, rw, N, T, 0.1, 1, 0, 0.0, g, small)
+
+
+@pytest.mark.parametrize("H,D,N,T", [(32, 3, 3, 2), (96, 33, 65, 3), (160, 10, 33, 4), (300, 40, 20, 9), (256, 31, 9, 257)])
+def test_policy_gradient_at_tile_edges(H, D, N, T):
+    """Widths on both sides of the tile widths (32, 64, 128, 256) and sums that end inside a block
+    of 32 terms; row counts on both sides of a chunk of 2048."""
+    import torch
+    from paper_2501_10709_amd import binding as B
+    S, K, sigma, key = 7 * D + 1, 2, 0.1, 5
+    actors = make_actor_weights(ActorConfig(n_actors=K, in_dim=S, hidden=H, out_dim=D, bias_std=0.1, seed_base=77))
+    rng = np.random.default_rng(H)
+    states = rng.normal(0.0, 0.5, (T, N, S)).astype(np.float32)
+    rew = rng.normal(0.0, 1.0, (T, N))
+    w = torch.as_tensor(pack_actor_weights(actors)).cuda()
+    ws = torch.empty(B.fm_pg_workspace_bytes(K, S, H, D, N, T), dtype=torch.uint8, device="cuda")
+    g = torch.empty(S * H + H + H * H + H + H * D + D, dtype=torch.float32, device="cuda")
+    B.fm_policy_gradient(K, S, H, D, w, 1, torch.as_tensor(states).cuda(), torch.as_tensor(rew).cuda(), N, T, sigma, key,
+                         0, 0.3, g, ws)
+    got = _unflatten(g.cpu().numpy().astype(np.float64), S, H, D)
+    want = OL.policy_gradient(actors, 1, states, rew, sigma, key, 0, 0.3)
+    for name in NAMES:
+        scale = np.abs(want[name]).max()
+        assert np.abs(got[name] - want[name]).max() <= 1e-5 * scale, name
+
+
+def test_policy_gradient_with_infinite_and_huge_inputs():
+    """An infinite state entry saturates its row's first layer and makes its own weight row's
+    gradient infinite or NaN; one beyond the bfloat16 range (3.39e38) is finite.  All other gradients are
+    those of float32 arithmetic with the same entries."""
+    import torch
+    from paper_2501_10709_amd import binding as B
+    S, H, D, K, N, T = 8, 64, 3, 1, 40, 3
+    per = S * H + H + H * H + H + H * D + D
+    g = torch.Generator(device="cuda").manual_seed(3)
+    w = torch.randn(per, generator=g, device="cuda") * 0.2
+    states = torch.randn((T, N, S), generator=g, device="cuda")
+    states[1, 7, 2] = float("inf")
+    states[2, 9, 5] = 3.4e38
+    rew = torch.randn((T, N), generator=g, device="cuda", dtype=torch.float64)
+    ws = torch.empty(B.fm_pg_workspace_bytes(K, S, H, D, N, T), dtype=torch.uint8, device="cuda")
+    got = torch.empty(per, device="cuda")
+    B.fm_policy_gradient(K, S, H, D, w, 0, states, rew, N, T, 0.1, 1, 0, 0.0, got, ws)
+    x = states.reshape(T * N, S).cpu()
+    o, p = 0, []
+    for shp in ((S, H), (H,), (H, H), (H,), (H, D), (D,)):
+        p.append(w[o:o + int(np.prod(shp))].cpu().reshape(shp))
+        o += int(np.prod(shp))
+    h1 = torch.tanh(x @ p[0] + p[1])
+    h2 = torch.tanh(h1 @ p[2] + p[3])
+    assert torch.isfinite(h2).all()
+    mu = torch.tanh(h2 @ p[4] + p[5])
+    eps = torch.empty((T, N, D), device="cuda")
+    for t in range(T):
+        B.fm_noise(1, 0, N, t, D, eps[t])
+    ret = (rew.sum(0) / N).float().cpu().repeat(T)[:, None]
+    g3 = ret * (0.1 * eps.reshape(T * N, D).cpu()) / 0.01 * (1 - mu * mu)
+    g2 = (g3 @ p[4].t()) * (1 - h2 * h2)
+    g1 = (g2 @ p[2].t()) * (1 - h1 * h1)
+    want = torch.cat([v.reshape(-1) for v in (x.t() @ g1, g1.sum(0), h1.t() @ g2, g2.sum(0), h2.t() @ g3, g3.sum(0))])
+    got = got.cpu()
+    row = torch.arange(per) // H
+    plain = ~((row == 2) | (row == 5)) | (torch.arange(per) >= S * H)
+    assert torch.isfinite(want[plain]).all()
+    err = (got - want)[plain].abs().max() / want[plain].abs().max()
+    assert err <= 1e-5, err
+    assert torch.equal(torch.isfinite(got), torch.isfinite(want))
