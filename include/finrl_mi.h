@@ -155,11 +155,12 @@ fm_status env_set_step_kernel(fm_env* env, int32_t kernel, int32_t envs_per_wave
 /* Tuning of the fused rollout (results stay within the bfloat16 tolerance; the environment
  * arithmetic is unchanged): schedule 0 picks, by shape and size, the resident schedule (weights
  * held on chip, eight environments per compute unit; K = 3, hidden 256, <= 31 stocks) when the
- * batch fits one workgroup per compute unit, else the streamed one (weights streamed from L2;
- * K = 3, hidden 256, <= 32 stocks), else the generic (runtime-shape) one; 1 skips the resident
- * schedule; 2 always takes the generic one; 3 takes the resident schedule whenever the shape
+ * batch fits one workgroup per compute unit and its wide form (up to 32 environments each; only
+ * with row_tiles 0) beyond that, else the streamed one (weights streamed from L2; K = 3, hidden
+ * 256, <= 32 stocks; results equal to the wide form's), else the generic (runtime-shape) one; 1
+ * skips the resident schedules; 2 always takes the generic one; 3 takes the resident schedule whenever the shape
  * allows it, whatever N.  row_tiles 1 or 2 sets the streamed schedule's 16 or 32 MFMA rows per
- * workgroup (0: by N); tile_envs the environments per workgroup (resident <= 8, streamed <= 16 *
+ * workgroup (0: by N); tile_envs the environments per workgroup (resident <= 8, wide <= 32, streamed <= 16 *
  * row_tiles; 0: fill the compute units).  FM_ERR_INVALID for NULL or out-of-range values. */
 fm_status env_set_fused_tuning(fm_env* env, int32_t schedule, int32_t row_tiles, int32_t tile_envs);
 void env_destroy(fm_env* env);

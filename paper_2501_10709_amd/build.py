@@ -15,7 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB_NAME = "libfinrl_mi.so"
 LIB_PATH = os.path.join(HERE, LIB_NAME)
-SOURCES = ["api.hip", "env_kernels.hip", "env_lane.hip", "ensemble_kernels.hip", "fused_rollout.hip", "fused_resident.hip", "metrics_kernels.hip", "crypto_serve.hip", "learner.hip"]
+SOURCES = ["api.hip", "env_kernels.hip", "env_lane.hip", "ensemble_kernels.hip", "fused_rollout.hip", "fused_resident.hip", "fused_wide.hip", "metrics_kernels.hip", "crypto_serve.hip", "learner.hip"]
 ARCH = "gfx950"
 
 HIPCC_FLAGS = [
@@ -30,10 +30,11 @@ HIPCC_FLAGS = [
 ]
 
 
-# Per-source extra flags.  The resident rollout keeps the second layer's weights in both register
-# files; its MFMA results go to the vector registers so that the accumulation registers hold
+# Per-source extra flags.  The resident rollouts keep the second layer's weights in both register
+# files; their MFMA results go to the vector registers so that the accumulation registers hold
 # weights only.
-EXTRA_FLAGS = {"fused_resident.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+EXTRA_FLAGS = {"fused_resident.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+               "fused_wide.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def _hipcc() -> str:

@@ -61,6 +61,11 @@ hipError_t launch_chunk_inputs(const EnvConst& C, const EnsDev& E, int t, int n,
 hipError_t launch_resident(const EnvConst& C, const EnvState& st, const EnsDev& E, FusedArgs F, float* eps_chunk,
                            float* mt_chunk, hipStream_t stream);
 
+// One chunk of the wide resident schedule (fused_wide.hip): the resident schedule's shapes, up to 32
+// environments per workgroup.
+hipError_t launch_wide_chunk(const EnvConst& C, const EnvState& st, const EnsDev& E, const FusedArgs& F,
+                             hipStream_t stream);
+
 // Returns hipSuccess and leaves *why empty on success; sets *why for unsupported shapes.
 hipError_t launch_fused_rollout(const EnvConst& C, const EnvState& st, const EnsDev& E, int t0,
                                 int n_steps, float sigma, uint64_t key, int64_t env_offset,

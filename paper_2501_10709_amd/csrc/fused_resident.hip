@@ -41,8 +41,8 @@
 #include "device_common.h"
 #include "fused.h"
 #include "mlp_device.h"
+#include "resident_device.h"
 #include "row_chain.h"
-
 
 
 namespace fm {
@@ -50,14 +50,7 @@ namespace fm {
 namespace {
 
 constexpr int kRT = 256;     // threads per workgroup
-constexpr int kRK = 3, kRH = 256, kRKK = 8;
-constexpr int kRX0 = 40;     // state-row stride (bfloat16): cash, <= 31 holdings, zeros
 constexpr int kRXS = 264;    // hidden-row stride (bfloat16)
-constexpr int kRIn = 256;    // market entries per day, (2 + I) * D <= 256
-// An input buffer in LDS: close[t] | close[t+1] in floats 0 .. 2D-1, ind[t+1] from float kRInd
-// (the fetch writes whole runs of 64 floats, so the two parts do not overlap).
-constexpr int kRInd = 64;
-constexpr int kRInBuf = kRInd + 256;
 // A float32 image of a step's state rows ([8][S], S = 1 + (2 + I) D <= 1 + kRIn), padded to whole
 // 16-byte units.
 constexpr int kRImg = kResRows * (kRIn + 4);
@@ -86,14 +79,6 @@ struct RLds {
 static_assert(RLds::total <= 160 * 1024, "LDS budget");
 static_assert(kRK * kRH % (64 * 3) == 0, "wavefronts 0-2 fetch equal shares of a table row");
 
-// An opaque zero: values derived from it are recomputed where they are used instead of being
-// hoisted out of the step loop and held in registers.
-__device__ __forceinline__ int opaque_zero() {
-  int z = 0;
-  asm volatile("" : "+s"(z));
-  return z;
-}
-
 // The layers run transposed: out[unit][env] = W^T x, the packed weight fragment as the A
 // operand and the activation rows as the B operand, so lane l of an accumulator holds units
 // 4(l/16) .. 4(l/16)+3 of its 16-unit tile for environment l mod 16.  The activation rows of the
@@ -113,33 +98,6 @@ __device__ __forceinline__ floatx4 merge_tiles(const floatx4& q0, const floatx4&
 __device__ __forceinline__ float tanh_sig(float x) {
   const float t = __builtin_amdgcn_exp2f(-2.8853900817779268f * x);  // e^{-2x}
   return fmaf(2.0f, __builtin_amdgcn_rcpf(1.0f + t), -1.0f);
-}
-
-// Four activations as bfloat16 (round to nearest even), 8 bytes.
-__device__ __forceinline__ uint2 pack_bf16x4(float a, float b, float c, float d) {
-  typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-  const bf16x2 lo = {static_cast<__bf16>(a), static_cast<__bf16>(b)};
-  const bf16x2 hi = {static_cast<__bf16>(c), static_cast<__bf16>(d)};
-  return uint2{__builtin_bit_cast(unsigned, lo), __builtin_bit_cast(unsigned, hi)};
-}
-
-// Trajectory stores go through buffer resources that cover the tile's rows of one step: a lane
-// with nothing to store passes an offset beyond the range, which the hardware drops, so the
-// stores need no branches; a trajectory that is not requested gets an empty range.
-constexpr int kNoStore = 1 << 30;  // beyond every range; adding a row offset stays below 2^31
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const void* base, size_t elem_offset, size_t elem_bytes,
-                                                            int n_elems) {
-  if (!base) return __builtin_amdgcn_make_buffer_rsrc(nullptr, 0, 0, 0x00020000);
-  return __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<char*>(static_cast<const char*>(base)) + elem_offset * elem_bytes, 0,
-      static_cast<int>(elem_bytes * n_elems), 0x00020000);
-}
-__device__ __forceinline__ void store_f32(__amdgpu_buffer_rsrc_t r, int byte_off, float v) {
-  __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, byte_off, 0, 0);
-}
-// A load through such a resource returns 0 beyond its range.
-__device__ __forceinline__ float load_f32(__amdgpu_buffer_rsrc_t r, int byte_off) {
-  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, byte_off, 0, 0));
 }
 
 // The three layers of one step for the wavefront's tiles.  Lane l's B operand is activation

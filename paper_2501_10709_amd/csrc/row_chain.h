@@ -75,68 +75,6 @@ __device__ __forceinline__ double row_sub_impl(double acc, double v, std::intege
   return acc;
 }
 
-// The buys of the wavefront's two environments (Section 3.1, readings 5-7).
-// If every row's cash covers the sum of its whole orders with a margin far above the rounding of
-// 32 subtractions, every whole order fits in sequence: the debits are subtracted in stock order
-// and every order fills.  Otherwise the buys run as a sequence of events, both rows in step: with
-// cash C, the next stock (in ascending order) that can change anything is the first one with a
-// buy order whose one-share debit fits C -- the stocks before it fill nothing and leave C as it
-// is.  A ballot per stock slot finds each row's next event; the lane owning that stock fills it
-// (the whole order if its debit fits C, else the partial fill) and keeps the fill, and its debit
-// reaches the rest of the row by a lane permute.
-__device__ __forceinline__ void buy_all(double& cash, int (&kown)[2], int lane, const BuySet (&B)[2], double one_p) {
-#pragma clang fp contract(off)
-  const int jl = lane & 15, rl = (lane >> 4) & 1, rbase = lane & 48;
-  const double total = row_sum(0.0, B[0].deb + B[1].deb);  // any order: only a bound
-  if (__builtin_amdgcn_ballot_w64(!(cash >= total * (1.0 + 0x1p-40))) == 0) {
-    cash = row_sub_impl(cash, B[0].deb, std::make_integer_sequence<int, 16>());
-    cash = row_sub_impl(cash, B[1].deb, std::make_integer_sequence<int, 16>());
-    kown[0] = pq_order(B[0].pq);
-    kown[1] = pq_order(B[1].pq);
-    return;
-  }
-  const bool buy0 = pq_order(B[0].pq) > 0, buy1 = pq_order(B[1].pq) > 0;
-  int dn = 0;  // the row's next stock to consider
-  for (int it = 0; it < 32; ++it) {
-    const unsigned long long b0 = __builtin_amdgcn_ballot_w64(buy0 && B[0].c1 <= cash && jl >= dn);
-    const unsigned long long b1 = __builtin_amdgcn_ballot_w64(buy1 && B[1].c1 <= cash && jl + 16 >= dn);
-    const unsigned m0 = static_cast<unsigned>(b0 & 0xffffu) | (static_cast<unsigned>(b1 & 0xffffu) << 16);
-    const unsigned m1 = static_cast<unsigned>((b0 >> 16) & 0xffffu) | (static_cast<unsigned>((b1 >> 16) & 0xffffu) << 16);
-    if ((m0 | m1) == 0) break;
-    const unsigned mine = rl == 0 ? m0 : m1;
-    const int e = mine != 0 ? __builtin_ctz(mine) : 64;  // the row's event stock (64: none)
-    const bool hi = e >= 16;
-    const bool owner = (e & 15) == jl && e < 32;
-    // The owner's fill of stock e: whole, or partial when only part of the order fits.
-    const double deb = hi ? B[1].deb : B[0].deb;
-    const long pq = hi ? B[1].pq : B[0].pq;
-    const bool fits = deb <= cash;
-    int k = fits ? pq_order(pq) : 0;
-    double debit = fits ? deb : 0.0;
-    if (owner && !fits) {
-      const double c1 = hi ? B[1].c1 : B[0].c1;
-      bool ok = true;
-      k = partial_fill_sel(cash, static_cast<double>(pq_price(pq)), c1, pq_order(pq), one_p, debit, ok);
-      if (!ok) {
-        double rc1 = __builtin_amdgcn_rcp(c1);
-        rc1 = fma(fma(-c1, rc1, 1.0), rc1, rc1);
-        k = partial_fill(cash, static_cast<double>(pq_price(pq)), rc1, pq_order(pq), one_p, debit);
-      }
-    }
-    if (owner) kown[hi ? 1 : 0] = k;
-    const int src = rbase + (e & 15);
-    const long dbits = __builtin_bit_cast(long, debit);
-    const int lo = __builtin_amdgcn_ds_bpermute(4 * src, static_cast<int>(dbits));
-    const int hb = __builtin_amdgcn_ds_bpermute(4 * src, static_cast<int>(dbits >> 32));
-    const double d_e = __builtin_bit_cast(
-        double, static_cast<long>((static_cast<unsigned long>(static_cast<unsigned>(hb)) << 32) | static_cast<unsigned>(lo)));
-    if (e < 32) {
-      cash = cash - d_e;
-      dn = e + 1;
-    }
-  }
-}
-
 // The row's cash before each lane's stock under the serial recurrence P(j + 1) = P(j) - x(j),
 // P(0) = start, x(j) held by lane j: carried along the row one lane per round by DPP row shifts
 // (lane 0 has no source and keeps start), so lane j's value is the exact serial result of j
@@ -154,14 +92,16 @@ __device__ __forceinline__ double row_prefix(double start, double x, double& tot
 }
 
 // The buys of the wavefront's two environments (Section 3.1, readings 5-7), by segments.
-// Fast path as in buy_all.  Otherwise, with cash C at the start of a segment, the candidates are
+// If every row's cash covers the sum of its whole orders with a margin far above the rounding of
+// 32 subtractions, every whole order fits in sequence: the debits are subtracted in stock order
+// and every order fills.  Otherwise, with cash C at the start of a segment, the candidates are
 // the stocks from dn on with a buy order whose one-share debit fits C (the others cannot buy: the
 // cash only falls during the buys).  Every candidate is assumed to fill its whole order; the row
 // prefix of their debits gives the cash each one meets, exactly as the serial recurrence would,
 // up to the first candidate e whose whole order does not fit that cash.  The candidates before e
 // fill whole; e buys what its cash allows (a partial fill, or nothing when one share does not
 // fit); the next segment starts after e.  A segment therefore covers a run of whole fills at the
-// cost of one prefix, where buy_all spends one event per stock.
+// cost of one prefix.
 __device__ __forceinline__ void buy_all_seg(double& cash, int (&kown)[2], int lane, const BuySet (&B)[2],
                                             double one_p) {
 #pragma clang fp contract(off)
@@ -232,6 +172,165 @@ __device__ __forceinline__ void buy_all_seg(double& cash, int (&kown)[2], int la
     cash = __builtin_bit_cast(
         double, static_cast<long>((static_cast<unsigned long>(static_cast<unsigned>(hb)) << 32) | static_cast<unsigned>(lo)));
     dn = e < 32 ? e + 1 : 32;
+  }
+}
+
+// row_sum, and row_prefix, of NQ independent sets step by step, so that their dependent chains fill
+// each other's latencies.
+template <int NQ, int L = 0>
+__device__ __forceinline__ void row_sums(double (&acc)[NQ], const double (&v)[NQ]) {
+#pragma clang fp contract(off)
+#pragma unroll
+  for (int n = 0; n < NQ; ++n) acc[n] = acc[n] + row_bcast<L>(v[n]);
+  if constexpr (L < 15) row_sums<NQ, L + 1>(acc, v);
+}
+template <int NQ>
+__device__ __forceinline__ void row_prefixes(const double (&start)[NQ], const double (&x)[NQ], double (&t)[NQ],
+                                             double (&total)[NQ]) {
+#pragma clang fp contract(off)
+  double d[NQ];
+#pragma unroll
+  for (int n = 0; n < NQ; ++n) t[n] = start[n];
+#pragma unroll
+  for (int r = 0; r < 15; ++r) {
+#pragma unroll
+    for (int n = 0; n < NQ; ++n) d[n] = t[n] - x[n];
+#pragma unroll
+    for (int n = 0; n < NQ; ++n) t[n] = row_shr1(t[n], d[n]);
+  }
+#pragma unroll
+  for (int n = 0; n < NQ; ++n) total[n] = row_bcast<15>(t[n] - x[n]);
+}
+
+// The same for NQ sets of four environments, one per 16-lane row (all four rows differ), the sets
+// side by side (the steps below are chains of dependent instructions that leave most issue slots
+// empty).  The first failure of a row usually leaves less cash than one share of its stock, and few
+// later stocks are cheaper, so after one segment the buys go on as events: each row's next stock
+// with a buy order whose one-share debit fits the cash buys its whole order or what the cash
+// allows.  Both forms are exact; an event costs about a third of a segment.
+template <int NQ>
+__device__ __forceinline__ void buy_all_seg4(double (&cash)[NQ], int (&kown)[NQ][2], int lane, const BuySet (&B)[NQ][2],
+                                             double one_p) {
+#pragma clang fp contract(off)
+  const int jl = lane & 15, rsh = lane & 48;  // rsh: this lane's row's bits in a ballot
+  bool covered = true;
+  double total[NQ], both[NQ];
+#pragma unroll
+  for (int n = 0; n < NQ; ++n) {
+    total[n] = 0.0;
+    both[n] = B[n][0].deb + B[n][1].deb;  // any order: only a bound
+  }
+  row_sums(total, both);
+#pragma unroll
+  for (int n = 0; n < NQ; ++n) covered = covered && cash[n] >= total[n] * (1.0 + 0x1p-40);
+  if (__builtin_amdgcn_ballot_w64(!covered) == 0) {
+#pragma unroll
+    for (int n = 0; n < NQ; ++n) {
+      cash[n] = row_sub_impl(cash[n], B[n][0].deb, std::make_integer_sequence<int, 16>());
+      cash[n] = row_sub_impl(cash[n], B[n][1].deb, std::make_integer_sequence<int, 16>());
+      kown[n][0] = pq_order(B[n][0].pq);
+      kown[n][1] = pq_order(B[n][1].pq);
+    }
+    return;
+  }
+  // One segment: every candidate's cash if those before it fill whole.
+  double at[2][NQ], mid[NQ], end[NQ];  // the cash that the lane's stocks meet; after 16; after them all
+  bool cand[2][NQ];
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    double x[NQ];
+#pragma unroll
+    for (int n = 0; n < NQ; ++n) {
+      cand[s][n] = pq_order(B[n][s].pq) > 0 && B[n][s].c1 <= cash[n];
+      x[n] = cand[s][n] ? B[n][s].deb : 0.0;
+    }
+    if (s == 0) row_prefixes(cash, x, at[0], mid);
+    else row_prefixes(mid, x, at[1], end);
+  }
+  int dn[NQ];  // the rows' next stocks to consider
+  bool more = false;
+  // Stock e of each row (32: none), whose lane holds its cash pe, buys whole or what pe allows; the
+  // row's cash becomes what is left, or `rest` where there is no such stock.
+  const auto fill = [&](const int (&e)[NQ], const double (&pe)[NQ], const double (&rest)[NQ]) {
+    bool slow = false, part[NQ], owner[NQ];
+    int k[NQ];
+    double nc[NQ];
+#pragma unroll
+    for (int n = 0; n < NQ; ++n) {
+      const bool hi = e[n] >= 16;
+      const double deb = hi ? B[n][1].deb : B[n][0].deb;
+      const long pq = hi ? B[n][1].pq : B[n][0].pq;
+      const double c1e = hi ? B[n][1].c1 : B[n][0].c1;
+      owner[n] = e[n] < 32 && (e[n] & 15) == jl;
+      const bool whole = deb <= pe[n];
+      bool ok;
+      double debit;
+      k[n] = partial_fill_sel(pe[n], static_cast<double>(pq_price(pq)), c1e, pq_order(pq), one_p, debit, ok);
+      part[n] = owner[n] && !whole && c1e <= pe[n] && !ok;
+      slow = slow || part[n];
+      k[n] = whole ? pq_order(pq) : c1e <= pe[n] ? k[n] : 0;
+      debit = whole ? deb : c1e <= pe[n] ? debit : 0.0;
+      nc[n] = owner[n] ? pe[n] - debit : rest[n];
+    }
+    if (__builtin_amdgcn_ballot_w64(slow) != 0) {
+#pragma unroll
+      for (int n = 0; n < NQ; ++n)
+        if (part[n]) {
+          const bool hi = e[n] >= 16;
+          const long pq = hi ? B[n][1].pq : B[n][0].pq;
+          const double c1e = hi ? B[n][1].c1 : B[n][0].c1;
+          double rc1 = __builtin_amdgcn_rcp(c1e), debit;
+          rc1 = fma(fma(-c1e, rc1, 1.0), rc1, rc1);
+          k[n] = partial_fill(pe[n], static_cast<double>(pq_price(pq)), rc1, pq_order(pq), one_p, debit);
+          nc[n] = pe[n] - debit;
+        }
+    }
+#pragma unroll
+    for (int n = 0; n < NQ; ++n) {
+      if (owner[n] && e[n] < 16) kown[n][0] = k[n];
+      if (owner[n] && e[n] >= 16) kown[n][1] = k[n];
+      const int src = e[n] < 32 ? rsh + (e[n] & 15) : lane;
+      const long nbits = __builtin_bit_cast(long, nc[n]);
+      const int lo = __builtin_amdgcn_ds_bpermute(4 * src, static_cast<int>(nbits));
+      const int hb = __builtin_amdgcn_ds_bpermute(4 * src, static_cast<int>(nbits >> 32));
+      cash[n] = __builtin_bit_cast(
+          double, static_cast<long>((static_cast<unsigned long>(static_cast<unsigned>(hb)) << 32) | static_cast<unsigned>(lo)));
+      dn[n] = e[n] < 32 ? e[n] + 1 : 32;
+    }
+  };
+  // The first stock of the row among two ballots (stocks 0-15, 16-31), or 32.
+  const auto first_of = [&](unsigned long long b0, unsigned long long b1) {
+    const unsigned mine = static_cast<unsigned>((b0 >> rsh) & 0xffffu) | (static_cast<unsigned>((b1 >> rsh) & 0xffffu) << 16);
+    return mine != 0 ? __builtin_ctz(mine) : 32;
+  };
+  int e[NQ];
+  double pe[NQ];
+#pragma unroll
+  for (int n = 0; n < NQ; ++n) {
+    e[n] = first_of(__builtin_amdgcn_ballot_w64(cand[0][n] && !(B[n][0].deb <= at[0][n])),
+                    __builtin_amdgcn_ballot_w64(cand[1][n] && !(B[n][1].deb <= at[1][n])));
+    if (cand[0][n] && jl < e[n]) kown[n][0] = pq_order(B[n][0].pq);
+    if (cand[1][n] && jl + 16 < e[n]) kown[n][1] = pq_order(B[n][1].pq);
+    pe[n] = e[n] >= 16 ? at[1][n] : at[0][n];
+    more = more || e[n] < 32;
+  }
+  if (__builtin_amdgcn_ballot_w64(more) == 0) {  // every row filled all its candidates whole
+#pragma unroll
+    for (int n = 0; n < NQ; ++n) cash[n] = end[n];
+    return;
+  }
+  fill(e, pe, end);
+  for (int it = 0; it < 32; ++it) {
+    more = false;
+#pragma unroll
+    for (int n = 0; n < NQ; ++n) {
+      e[n] = first_of(
+          __builtin_amdgcn_ballot_w64(pq_order(B[n][0].pq) > 0 && B[n][0].c1 <= cash[n] && jl >= dn[n]),
+          __builtin_amdgcn_ballot_w64(pq_order(B[n][1].pq) > 0 && B[n][1].c1 <= cash[n] && jl + 16 >= dn[n]));
+      more = more || e[n] < 32;
+    }
+    if (__builtin_amdgcn_ballot_w64(more) == 0) break;
+    fill(e, cash, cash);
   }
 }
 
