@@ -13,8 +13,13 @@
 // layer 3 (its 32 units) into LDS partial sums; then one lane of the environment wavefront per
 // environment adds the four partial sums in a fixed order, applies the ensemble rule and the
 // exploration draw (computed while the MLP ran), trades in float64, updates the running
-// statistics and writes the next state row.  Three workgroup barriers per tick.  The
-// environment's state stays in that lane's registers for the item.
+// statistics and writes the next state row.  Four workgroup barriers per tick.
+//
+// Bound by the latency of a tick: one MLP wavefront per SIMD (a wavefront's slice of W2 is 160
+// registers), so the layers run as stages fenced against reordering, each stage's products beside
+// the activations of the one before.  A tick of a 64-environment tile with five agents: 11.5 k
+// cycles (layer 1 2.9 k, layer 2 and 3 6 k, softmax 1.4 k, trade 1.9 k), 4.8 us from 6.7 with the
+// layers in the compiler's order and the market row waited for inside layer 1.
 //
 // Scheduler.  Host-side: a FIFO queue, a first-fit allocator over the caller's device pool, the
 // active set, and per-chunk lists of (request, tile) items copied from pinned staging.
@@ -82,22 +87,28 @@ struct ChunkArgs {
 
 typedef __attribute__((ext_vector_type(8))) short s16x8;
 
-// relu(x) rounded to bfloat16 for eight accumulators.  Rounding keeps the sign, so the ReLU is
-// applied after it as a signed 16-bit max with zero on the bfloat16 bit patterns (negative
-// values, -0 included, have the sign bit set).
-__device__ __forceinline__ bf16x8 pack_relu(floatx4 a, floatx4 b) {
-  bf16x8 r;
-  r[0] = static_cast<__bf16>(a[0]);
-  r[1] = static_cast<__bf16>(a[1]);
-  r[2] = static_cast<__bf16>(a[2]);
-  r[3] = static_cast<__bf16>(a[3]);
-  r[4] = static_cast<__bf16>(b[0]);
-  r[5] = static_cast<__bf16>(b[1]);
-  r[6] = static_cast<__bf16>(b[2]);
-  r[7] = static_cast<__bf16>(b[3]);
-  const s16x8 m = __builtin_elementwise_max(__builtin_bit_cast(s16x8, r), s16x8{0, 0, 0, 0, 0, 0, 0, 0});
-  return __builtin_bit_cast(bf16x8, m);
+// relu(x) of two values rounded to bfloat16.  Rounding keeps the sign, so the ReLU is applied after
+// it as a signed 16-bit max with zero on the bfloat16 bit patterns (negative values, -0 included,
+// have the sign bit set).
+__device__ __forceinline__ unsigned round2(float a, float b) {
+  typedef float f2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(unsigned, __builtin_convertvector(f2{a, b}, b2));
 }
+__device__ __forceinline__ unsigned relu2(unsigned v) {
+  typedef short s2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(unsigned, __builtin_elementwise_max(__builtin_bit_cast(s2, v), s2{0, 0}));
+}
+// The eight activations of two accumulators in eight steps: four roundings, four maxima.
+typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+__device__ __forceinline__ void relu_step(int i, const floatx4& a, const floatx4& b, u32x4& r) {
+  if (i == 0) r[0] = round2(a[0], a[1]);
+  if (i == 1) r[1] = round2(a[2], a[3]);
+  if (i == 2) r[2] = round2(b[0], b[1]);
+  if (i == 3) r[3] = round2(b[2], b[3]);
+  if (i >= 4) r[i - 4] = relu2(r[i - 4]);
+}
+__device__ __forceinline__ void fence() { __builtin_amdgcn_sched_barrier(0); }
 
 __device__ __forceinline__ floatx4 mfma16(s16x4 a, s16x4 b, floatx4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
@@ -236,60 +247,120 @@ __global__ __launch_bounds__(kNT, 1) void crypto_chunk_kernel(ChunkArgs a) {
 
     for (int s = 0; s < nt; ++s) {
       const int64_t t = t0 + s;
-      if (mlp_wave) {
-        // Layer 1: hidden units 32w.. of every agent for every block of 16 environments.
-        s16x4 xb[R];
-#pragma unroll
-        for (int b = 0; b < R; ++b) xb[b] = *reinterpret_cast<const s16x4*>(xs + (b * 16 + e16) * kF + 4 * g);
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-          const s16x4 wa0 = w1s[((k * kNW + wave) * 2 + 0) * 64 + lane];
-          const s16x4 wa1 = w1s[((k * kNW + wave) * 2 + 1) * 64 + lane];
-          const floatx4 c0 = *reinterpret_cast<const floatx4*>(b1s + k * kH + 32 * wave + 4 * g);
-          const floatx4 c1 = *reinterpret_cast<const floatx4*>(b1s + k * kH + 32 * wave + 16 + 4 * g);
-#pragma unroll
-          for (int b = 0; b < R; ++b)
-            hs[((k * kNW + wave) * R + b) * 64 + lane] = pack_relu(mfma16(wa0, xb[b], c0), mfma16(wa1, xb[b], c1));
-        }
-      } else if (valid) {
-        // Next tick's market row, staged in LDS while the MLP runs.
-        const int64_t tick = tick0 + s;
-        sp1[ce] = a.mid[tick + 1];
-        float4 f[4];
-        load_feat(a.feat, tick + 1, f);
+      // Next tick's market row (the environment wavefront): requested during layer 1 and put into LDS
+      // there, or, where the layers are long enough to cover its way from memory, during layer 2
+      // (24 requests of five agents in 64-environment tiles 7.3 ms against 8.0 with it in layer 1; the
+      // smaller tiles are 5 to 15% slower with it in layer 2).
+      constexpr bool kStageLate = R * K >= 12;
+      const auto stage_row = [&](double mid, const float4 (&f)[4]) {
+        sp1[ce] = mid;
 #pragma unroll
         for (int i = 0; i < 4; ++i) sf[ce * 4 + i] = f[i];
+      };
+      double next_mid = 0.0;
+      float4 next_f[4];
+      if (mlp_wave) {
+        // Layer 1: hidden units 32w.. of every agent for every block of 16 environments, in (agent,
+        // block) stages: the products of stage i + 1 are issued before the activations of stage i,
+        // the next agent's operands requested a stage ahead.
+        constexpr int NB = K * R;
+        s16x4 xb[R], wa[2][2];
+        floatx4 cb[2][2], acc[2][2];
+#pragma unroll
+        for (int b = 0; b < R; ++b) xb[b] = *reinterpret_cast<const s16x4*>(xs + (b * 16 + e16) * kF + 4 * g);
+        const auto operands = [&](int k) {
+#pragma unroll
+          for (int tt = 0; tt < 2; ++tt) {
+            wa[k & 1][tt] = w1s[((k * kNW + wave) * 2 + tt) * 64 + lane];
+            cb[k & 1][tt] = *reinterpret_cast<const floatx4*>(b1s + k * kH + 32 * wave + 16 * tt + 4 * g);
+          }
+        };
+        const auto products = [&](int i) {
+#pragma unroll
+          for (int tt = 0; tt < 2; ++tt) acc[i & 1][tt] = mfma16(wa[i / R & 1][tt], xb[i % R], cb[i / R & 1][tt]);
+        };
+        operands(0);
+        if (K > 1) operands(1);
+        products(0);
+        fence();
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+          if (i + 1 < NB) products(i + 1);
+          if (i % R == R - 1 && i / R + 2 < K) operands(i / R + 2);
+          fence();
+          u32x4 h;
+#pragma unroll
+          for (int q = 0; q < 8; ++q) relu_step(q, acc[i & 1][0], acc[i & 1][1], h);
+          hs[((i / R * kNW + wave) * R + i % R) * 64 + lane] = __builtin_bit_cast(bf16x8, h);
+          fence();
+        }
+      } else if (valid) {
+        const int64_t tick = tick0 + s;
+        next_mid = a.mid[tick + 1];
+        load_feat(a.feat, tick + 1, next_f);
+        if (!kStageLate) stage_row(next_mid, next_f);
       }
       __syncthreads();
       int explore_act = -1;
       if (mlp_wave) {
-        // Layer 2 (this wavefront's 32 units) and its share of layer 3.
+        // Layer 2 (this wavefront's 32 units) and its share of layer 3, in (agent, block) stages: the
+        // eight products of stage i are spaced by the eight steps of stage i - 1's activations; stage
+        // i + 1's inputs, and the next agent's biases and W3 fragment, are requested a stage ahead.
+        // (Left to itself the compiler runs each stage as one chain of LDS reads, products,
+        // activations and the layer-3 product: about 450 cycles a stage, 300 now, of which the
+        // products take 153.)
+        constexpr int NB = K * R;
+        bf16x8 hc[2][4], w3;
+        floatx4 cb[2], acc[2][2];
+        const auto inputs = [&](int i) {
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-          const floatx4 c0 = *reinterpret_cast<const floatx4*>(b2s + k * kH + 32 * wave + 4 * g);
-          const floatx4 c1 = *reinterpret_cast<const floatx4*>(b2s + k * kH + 32 * wave + 16 + 4 * g);
-          bf16x8 w3 = {};
+          for (int kk = 0; kk < 4; ++kk) hc[i & 1][kk] = hs[((i / R * kNW + kk) * R + i % R) * 64 + lane];
+        };
+        const auto biases = [&](int k) {
+#pragma unroll
+          for (int tt = 0; tt < 2; ++tt) cb[tt] = *reinterpret_cast<const floatx4*>(b2s + k * kH + 32 * wave + 16 * tt + 4 * g);
+        };
+        const auto load_w3 = [&](int k) {
+          w3 = bf16x8{};
           if (e16 < kA) w3 = w3s[(k * kNW + wave) * 12 + g * 3 + e16];
+        };
+        const auto finish = [&](int i, const u32x4& h) {
+          const floatx4 q = mfma_bf16(w3, __builtin_bit_cast(bf16x8, h), floatx4{0.0f, 0.0f, 0.0f, 0.0f});
+          if (lane < 16) ps[((wave * K + i / R) * R + i % R) * 16 + lane] = q;
+        };
+        inputs(0);
+        biases(0);
+        load_w3(0);
+        u32x4 h;
 #pragma unroll
-          for (int b = 0; b < R; ++b) {
-            bf16x8 hc[4];
+        for (int i = 0; i < NB; ++i) {
+          const int k = i / R;
+          if (i + 1 < NB) inputs(i + 1);
+          fence();
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) hc[kk] = hs[((k * kNW + kk) * R + b) * 64 + lane];
-            floatx4 acc0 = c0, acc1 = c1;
+          for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) {
-              acc0 = mfma_bf16(w2[k][0][kk], hc[kk], acc0);
-              acc1 = mfma_bf16(w2[k][1][kk], hc[kk], acc1);
+            for (int tt = 0; tt < 2; ++tt) {
+              acc[i & 1][tt] = mfma_bf16(w2[k][tt][kk], hc[i & 1][kk], kk == 0 ? cb[tt] : acc[i & 1][tt]);
+              if (i > 0) relu_step(2 * kk + tt, acc[(i - 1) & 1][0], acc[(i - 1) & 1][1], h);
+              if (kk == 1 && tt == 0 && i % R == R - 1 && k + 1 < K) biases(k + 1);
+              fence();
             }
-            const floatx4 q = mfma_bf16(w3, pack_relu(acc0, acc1), floatx4{0.0f, 0.0f, 0.0f, 0.0f});
-            if (lane < 16) ps[((wave * K + k) * R + b) * 16 + lane] = q;
-          }
+          if (i > 0) finish(i - 1, h);
+          if (i > 0 && i % R == 0) load_w3(k);  // for stage i's own layer-3 product, in the next stage
+          fence();
         }
-      } else if (valid && a.eps > 0.0f) {
-        // Exploration draw for this tick, while the MLP runs.
-        uint64_t c0 = static_cast<uint64_t>(n), c1 = static_cast<uint64_t>(t), c2 = 0, c3 = 0;
-        philox4x64_10(c0, c1, c2, c3, d.key, 1);
-        if (uniform_from_word(c0) < a.eps) explore_act = static_cast<int>(static_cast<uint32_t>(c1 >> 32) % 3u);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) relu_step(q, acc[(NB - 1) & 1][0], acc[(NB - 1) & 1][1], h);
+        finish(NB - 1, h);
+      } else if (valid) {
+        if (a.eps > 0.0f) {
+          // Exploration draw for this tick, while the MLP runs.
+          uint64_t c0 = static_cast<uint64_t>(n), c1 = static_cast<uint64_t>(t), c2 = 0, c3 = 0;
+          philox4x64_10(c0, c1, c2, c3, d.key, 1);
+          if (uniform_from_word(c0) < a.eps) explore_act = static_cast<int>(static_cast<uint32_t>(c1 >> 32) % 3u);
+        }
+        if (kStageLate) stage_row(next_mid, next_f);
       }
       __syncthreads();
       // One thread per (agent, environment): the agent's action values from the four partial
@@ -320,7 +391,7 @@ __global__ __launch_bounds__(kNT, 1) void crypto_chunk_kernel(ChunkArgs a) {
       }
       __syncthreads();
       // One lane per environment: ensemble rule, exploration, trade, statistics, next state row.
-      if (valid) {
+      if (!mlp_wave && valid) {
         float avg[kA] = {0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int k = 0; k < K; ++k) {
