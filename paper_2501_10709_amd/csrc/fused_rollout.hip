@@ -14,7 +14,7 @@
 //     owns fixed output tiles and walks a compile-time sequence of weight fragments (all layers
 //     of all actors), keeping DEPTH k-steps of fragments in flight in registers.  The sequence
 //     wraps around, so the first fragments of the next step load while the trading chain runs.
-//   * generic (any supported shape): four wavefronts, runtime loops, one fragment at a time.
+//   * generic (any supported shape): eight wavefronts, runtime loops, a layer of all actors at a time.
 #include <algorithm>
 #include <cstring>
 #include <utility>
@@ -22,6 +22,7 @@
 #include "device_common.h"
 #include "fused.h"
 #include "mlp_device.h"
+#include "row_chain.h"
 
 namespace fm {
 
@@ -38,11 +39,12 @@ __device__ __forceinline__ void static_for(Fn&& f) {
   static_for_impl(f, std::make_integer_sequence<int, N>());
 }
 
-// LDS layout shared by both schedules.
+// LDS layout of the generic schedule.
 struct FusedLds {
-  __bf16 *x0, *x1, *x2;  // state rows, layer-1 and layer-2 outputs
+  __bf16* x0;            // state rows
+  __bf16* x1;            // [areas][MR][sth] hidden outputs, one area per actor of a pass
   float* abar;           // [MR][DS] ensemble mean
-  float* act;            // [MR][D] noisy clipped action
+  float* act;            // [MR][D] noise of the step, then the noisy clipped action
   int* hold;             // [MR][D] holdings (the trading state, resident for the whole rollout)
   int* qty;              // [MR][D] executed shares
   float* env;            // [MR][DS] cash entry, holdings entries of the state rows
@@ -50,16 +52,16 @@ struct FusedLds {
   float* mkt;            // [(1+I)*D] scaled new close, new indicators
   ChainLds chain;        // the chain's scratch and the views above
 
-  __host__ __device__ static size_t bytes(int MR, int st0, int sth, int D, int I) {
+  __host__ __device__ static size_t bytes(int MR, int st0, int sth, int D, int I, int areas) {
     const ChainShape Z = ChainShape::of(D);
     const size_t DS = D + 1;
     size_t b = Z.scratch_bytes(MR);
-    b += sizeof(__bf16) * MR * (static_cast<size_t>(st0) + 2 * sth);
+    b += sizeof(__bf16) * MR * (static_cast<size_t>(st0) + static_cast<size_t>(areas) * sth);
     b += sizeof(float) * MR * DS * 2 + sizeof(int) * MR * D * 2 + sizeof(float) * MR * D;
     b += sizeof(float) * (Z.DP + D + (1 + I) * D);
     return (b + 64 + 15) / 16 * 16;
   }
-  __device__ void carve(unsigned char* smem, int MR, int st0, int sth, int D) {
+  __device__ void carve(unsigned char* smem, int MR, int st0, int sth, int D, int areas) {
     const ChainShape Z = ChainShape::of(D);
     const int DS = D + 1;
     unsigned char* p = chain.carve_scratch(smem, Z, MR);
@@ -67,8 +69,7 @@ struct FusedLds {
     const size_t off = (static_cast<size_t>(p - smem) + 15) / 16 * 16;
     x0 = reinterpret_cast<__bf16*>(smem + off);
     x1 = x0 + MR * st0;
-    x2 = x1 + MR * sth;
-    abar = reinterpret_cast<float*>(x2 + MR * sth);
+    abar = reinterpret_cast<float*>(x1 + areas * MR * sth);
     env = abar + MR * DS;
     act = env + MR * DS;
     hold = reinterpret_cast<int*>(act + MR * D);
@@ -95,49 +96,98 @@ __device__ __forceinline__ __attribute__((address_space(1))) T* gbl(T* p) {
   return (__attribute__((address_space(1))) T*)p;
 }
 
-// The environment half of a step, shared by both schedules.  NT threads per workgroup.
+constexpr size_t kBatchedMaxLds = 160 * 1024 - 256;  // the batched kernel's own item slot takes a little
+
+constexpr int kGenericWaves = 8, kGenericThreads = 64 * kGenericWaves;
+// The first wavefronts run the environments' serial parts, a share each (a partial fill costs every
+// environment of its wavefront); the others what does not depend on them.
+constexpr int kOwnerWaves = 4, kIdleThreads = kGenericThreads - 64 * kOwnerWaves;
+
+// The environment half of a step of the generic schedule.  NT threads per workgroup.
 template <int NT>
 struct EnvPhase {
   const EnvConst& C;
   const FusedArgs& F;
   FusedLds& L;
-  int tid, lane, wave, n0, M, S_pad, st0;
+  int tid, lane, wave, n0, M, st0;
+  int me;  // owner lanes: the tile's environment
+ 
   float inv_d, inv_g;
   int G;
 
-  // Market rows of day tn (and the trading day tn-1 when trading) into LDS.
-  __device__ void stage_market(int tn, bool with_trade_day) {
+  // Closes of day tn into LDS (the ones there become the trading day's), and its market entries.
+  __device__ void stage_closes(int tn) {
     const int D = C.D;
     for (int d = tid; d < D; d += NT) {
-      if (with_trade_day) L.px[d] = gbl(C.close)[static_cast<size_t>(tn - 1) * D + d];
-      const float pn = gbl(C.close)[static_cast<size_t>(tn) * D + d];
-      L.pn[d] = pn;
-      L.mkt[d] = pn * C.price_scale;
+      L.px[d] = L.pn[d];
+      L.pn[d] = gbl(C.close)[static_cast<size_t>(tn) * D + d];
     }
+  }
+  __device__ void stage_market(int tn) {
+    const int D = C.D;
+    for (int d = tid; d < D; d += NT) L.mkt[d] = gbl(C.close)[static_cast<size_t>(tn) * D + d] * C.price_scale;
     for (int i = tid; i < C.I * D; i += NT) L.mkt[D + i] = gbl(C.ind)[static_cast<size_t>(tn) * C.I * D + i];
   }
 
-  // a = clip(a_bar + sigma * eps, -1, 1) into LDS (and the action trajectory).
-  __device__ void actions(int t, size_t row_base) {
-    const int D = C.D, DS = D + 1;
-    for (int i = tid; i < M * G; i += NT) {
+  // close[tn] and ind[tn] in registers: value i0 + nt * j per thread i0 >= 0 of a group of nt.
+  template <int R>
+  __device__ __forceinline__ void fetch_market(float (&mk)[R], int tn, int i0, int nt) {
+    const int D = C.D, n = (1 + C.I) * D;
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      const int i = i0 + nt * j;
+      if (i < n)
+        mk[j] = i < D ? gbl(C.close)[static_cast<size_t>(tn) * D + i]
+                      : gbl(C.ind)[static_cast<size_t>(tn) * C.I * D + (i - D)];
+    }
+  }
+  template <int R>
+  __device__ __forceinline__ void put_closes(const float (&mk)[R], int i0, int nt) {
+    const int D = C.D;
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      const int i = i0 + nt * j;
+      if (i < D) {
+        L.px[i] = L.pn[i];
+        L.pn[i] = mk[j];
+      }
+    }
+  }
+  template <int R>
+  __device__ __forceinline__ void put_market(const float (&mk)[R], int i0, int nt) {
+    const int D = C.D, n = (1 + C.I) * D;
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      const int i = i0 + nt * j;
+      if (i < n) L.mkt[i] = i < D ? mk[j] * C.price_scale : mk[j];
+    }
+  }
+
+  // The noise of day t into the action rows (threads i0, i0 + nt, ...).
+  __device__ void draw(int t, int i0, int nt) {
+    if (F.sigma == 0.0f) return;
+    const int D = C.D;
+    for (int i = i0; i < M * G; i += nt) {
       const int m = div_small(i, inv_g);
       const int g = i - m * G;
-      float z[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-      if (F.sigma != 0.0f)
-        noise_block(F.key, static_cast<uint64_t>(F.env_offset + n0 + m), static_cast<uint64_t>(t),
-                    static_cast<uint64_t>(g), z);
+      float z[4];
+      noise_block(F.key, static_cast<uint64_t>(F.env_offset + n0 + m), static_cast<uint64_t>(t),
+                  static_cast<uint64_t>(g), z);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int d = 4 * g + r;
-        if (d < D) {
-          float a = L.abar[m * DS + d];
-          if (F.sigma != 0.0f) a = a + F.sigma * z[r];
-          a = fminf(fmaxf(a, -1.0f), 1.0f);
-          L.act[m * D + d] = a;
-          if (F.act_traj) gbl(F.act_traj)[(row_base + m) * D + d] = a;
-        }
-      }
+      for (int r = 0; r < 4; ++r)
+        if (4 * g + r < D) L.act[m * D + 4 * g + r] = z[r];
+    }
+  }
+
+  // a = clip(a_bar + sigma * eps, -1, 1) over the noise in LDS (and into the action trajectory).
+  __device__ void actions(size_t row_base) {
+    const int D = C.D;
+    for (int i = tid; i < M * D; i += NT) {
+      float a = L.abar[i + div_small(i, inv_d)];  // rows of D + 1
+      if (F.sigma != 0.0f) a = a + F.sigma * L.act[i];
+      a = fminf(fmaxf(a, -1.0f), 1.0f);
+      L.act[i] = a;
+      if (F.act_traj) gbl(F.act_traj)[row_base * D + i] = a;
     }
   }
 
@@ -145,68 +195,74 @@ struct EnvPhase {
   __device__ void env_entries(bool owner, double cash) {
     if (!owner) return;
     const int D = C.D, DS = D + 1;
-    float* erow = L.env + lane * DS;
-    const int* hrow = L.hold + lane * D;
+    float* erow = L.env + me * DS;
+    const int* hrow = L.hold + me * D;
     erow[0] = static_cast<float>(cash * static_cast<double>(C.cash_scale));
     for (int d = 0; d < D; ++d) erow[1 + d] = static_cast<float>(hrow[d]) * C.hold_scale;
   }
 
   // One step of the trading chain: parallel pre-terms (all threads), the serial cash recurrence
   // (owner lanes), parallel post-terms (all threads).  Returns the reward in the owner lanes.
-  // Entered and left with all threads synchronised.
-  __device__ double chain(bool owner, double& cash, double& asset, double& cumrew) {
+  // Entered and left with all threads synchronised.  While the recurrence runs, the wavefronts past
+  // the owners' run meanwhile(), with the action rows free and the state rows still the last ones;
+  // staged() runs on all threads after it.
+  template <class Fn, class Gn>
+  __device__ double chain(bool owner, double& cash, double& asset, double& cumrew, Fn meanwhile, Gn staged) {
     const ChainShape Z = ChainShape::of(C.D);
     const ChainLds& CL = L.chain;
     chain_day_terms(CL, Z, tid, NT, C.one_p);
     chain_pairs_a(CL, Z, M, tid, NT, C.hmax_f, C.one_m, C.one_p);
     __syncthreads();
     if (owner)
-      chain_serial(cash, CL.pro + lane * Z.RD, CL.deb + lane * Z.RD, CL.c1, CL.rc1, CL.qd + lane * Z.RI, CL.px,
-                   CL.kq + lane * Z.RI, Z.DP, C.one_p);
+      chain_serial(cash, CL.pro + me * Z.RD, CL.deb + me * Z.RD, CL.c1, CL.rc1, CL.qd + me * Z.RI, CL.px,
+                   CL.kq + me * Z.RI, Z.DP, C.one_p);
+    if (wave >= kOwnerWaves) meanwhile();
     __syncthreads();
+    staged();
     chain_pairs_c(CL, Z, M, tid, NT, C.hold_scale);
     __syncthreads();
     double r = 0.0;
     if (owner) {
-      const double v_new = chain_value(cash, CL.val + lane * Z.RD, Z.DP);
+      const double v_new = chain_value(cash, CL.val + me * Z.RD, Z.DP);
       r = (v_new - asset) * C.reward_scale;
       cumrew = cumrew + r;
       asset = v_new;
-      L.env[lane * Z.DS] = static_cast<float>(cash * static_cast<double>(C.cash_scale));
+      L.env[me * Z.DS] = static_cast<float>(cash * static_cast<double>(C.cash_scale));
     }
     return r;
   }
 
-  // State rows: bfloat16 into x0 for the next first layer, float32 into the trajectory.  With
-  // the split first layer (split_pad > 0) x0 holds only the per-environment entries [cash,
-  // holdings] in split_pad columns; the market entries reach layer 1 through the day's table.
-  // The (row, column) pairs are spread over all threads: consecutive threads write consecutive
-  // entries of the tile's contiguous trajectory rows.
-  __device__ void assemble(float* traj, int split_pad = 0) {
+  // The state row entries in columns first, first + 64, ... (one lane's) of rows m0, m0 + dm, ...:
+  // put(m, f, e, v) for column f, e >= 0 the environment entry that it is (-1: a market entry).  A
+  // lane keeps its column over the rows, so that a market entry is read once and what a column holds
+  // is decided once.
+  template <class Put>
+  __device__ __forceinline__ void state_rows(int first, int m0, int dm, Put put) {
     const int D = C.D, DS = D + 1, S = C.S;
-    const int W = split_pad > 0 ? S : S_pad;  // columns visited per row
-    const float inv_w = 1.0f / static_cast<float>(W);
-#pragma unroll 2
-    for (int i = tid; i < M * W; i += NT) {
-      const int m = div_small(i, inv_w);
-      const int f = i - m * W;
-      float v = 0.0f;
-      if (f < S) {
-        if (f == 0) v = L.env[m * DS];
-        else if (f <= D) v = L.mkt[f - 1];
-        else if (f <= 2 * D) v = L.env[m * DS + f - D];
-        else v = L.mkt[f - 1 - D];
-        if (traj) gbl(traj)[static_cast<size_t>(m) * S + f] = v;
+    for (int f = first; f < S; f += 64) {
+      const bool env = f == 0 || (f > D && f <= 2 * D);
+      const int e = !env ? -1 : f == 0 ? 0 : f - D;
+      float v = env ? 0.0f : L.mkt[f <= D ? f - 1 : f - 1 - D];
+      for (int m = m0; m < M; m += dm) {
+        if (env) v = L.env[m * DS + e];
+        put(m, f, e, v);
       }
-      if (split_pad == 0) L.x0[m * st0 + f] = static_cast<__bf16>(v);
     }
-    if (split_pad > 0) {
-      const float inv_p = 1.0f / static_cast<float>(split_pad);
-      for (int i = tid; i < M * split_pad; i += NT) {
-        const int m = div_small(i, inv_p);
-        const int f = i - m * split_pad;
-        L.x0[m * st0 + f] = static_cast<__bf16>(f <= D ? L.env[m * DS + f] : 0.0f);
-      }
+  }
+  // float32 into the trajectory (wavefronts w = 0 .. nw-1).
+  __device__ void store_states(float* traj, int w, int nw) {
+    const int S = C.S;
+    state_rows(lane, w, nw, [&](int m, int f, int, float v) { gbl(traj)[static_cast<size_t>(m) * S + f] = v; });
+  }
+  // bfloat16 into x0 for the next first layer.  With the split first layer x0 holds only the
+  // per-environment entries [cash, holdings]; the market entries reach layer 1 through the day's table.
+  __device__ void assemble(bool split) {
+    if (split) {
+      const int DS = C.D + 1;
+      for (int m = wave; m < M; m += NT / 64)
+        for (int e = lane; e < DS; e += 64) L.x0[m * st0 + e] = static_cast<__bf16>(L.env[m * DS + e]);
+    } else {
+      state_rows(lane, wave, NT / 64, [&](int m, int f, int, float v) { L.x0[m * st0 + f] = static_cast<__bf16>(v); });
     }
   }
 
@@ -219,31 +275,135 @@ struct EnvPhase {
   // Load the tile's state into the owner lanes (holdings into LDS).
   __device__ void load_state(bool owner, const EnvState& st, double& cash, double& asset, double& cumrew) {
     if (!owner) return;
-    const int D = C.D, N = C.N, n = n0 + lane;
+    const int D = C.D, N = C.N, n = n0 + me;
     cash = st.cash[n];
     asset = st.asset[n];
     cumrew = st.cumrew[n];
-    for (int d = 0; d < D; ++d) L.hold[lane * D + d] = st.hold[static_cast<size_t>(d) * N + n];
+    for (int d = 0; d < D; ++d) L.hold[me * D + d] = st.hold[static_cast<size_t>(d) * N + n];
   }
   __device__ void store_state(bool owner, const EnvState& st, double cash, double asset, double cumrew) {
     if (!owner) return;
-    const int D = C.D, N = C.N, n = n0 + lane;
+    const int D = C.D, N = C.N, n = n0 + me;
     st.cash[n] = cash;
     st.asset[n] = asset;
     st.cumrew[n] = cumrew;
-    for (int d = 0; d < D; ++d) st.hold[static_cast<size_t>(d) * N + n] = L.hold[lane * D + d];
+    for (int d = 0; d < D; ++d) st.hold[static_cast<size_t>(d) * N + n] = L.hold[me * D + d];
   }
 };
 
 // ------------------------------------------------------------------------------------------
-// Generic MLP schedule (runtime shapes): wavefront w owns output tiles w, w+4, ...; the weight
-// fragments of the next four k-steps are in flight in a register ring while the current ones are
-// multiplied (the ensemble MLP's layer loop).  The epilogue gets (row tile, slot i, tile c).
+// Generic MLP schedule (runtime shapes): eight wavefronts, all actors of a pass (up to kPass)
+// together.  A layer is bound by the latency of its weights and by the barriers around it, not by
+// its products, so each of the three is passed once per step rather than once per actor: a
+// wavefront owns output tiles c0, c0 + 8, ... of every actor, and RING k-steps of all their
+// fragments are in flight.  KP actors, TJ tiles: both known, so the loop has no branches and
+// the waits are for the fragments that are needed.
 // ------------------------------------------------------------------------------------------
-template <int ROWT, int TMAX, class Epi>
-__device__ __forceinline__ void layer_bf16(const __bf16* sin, int ist, int kin_pad, const bf16x8* W,
-                                           int ntiles, int wave, int lane, Epi epi) {
-  mlp_layer<kBF16, TMAX, ROWT, 4, Epi, 4>(sin, ist, kin_pad, W, ntiles, wave, lane, epi);
+constexpr int kPass = 3;
+
+struct PassLayer {
+  const unsigned char* w;  // the first actor's packed fragments [tile][KK][64 lanes][16 bytes]
+  size_t wstride;          // bytes from one actor's to the next one's
+  const __bf16* in;        // the first actor's activation rows, of stride ist
+  int astride, ist, KK, c0, kbeg, kend;
+};
+
+template <int ROWT, int KP, int TJ, int RING, int KM, int TM>
+__device__ __forceinline__ void pass_products(const PassLayer& P, int lane, floatx4 (&acc)[KM][ROWT][TM]) {
+  typedef const __attribute__((address_space(1))) unsigned char* gptr;
+  gptr W[KP][TJ];
+#pragma unroll
+  for (int k = 0; k < KP; ++k)
+#pragma unroll
+    for (int j = 0; j < TJ; ++j)
+      W[k][j] = (gptr)P.w + k * P.wstride + (static_cast<size_t>((P.c0 + kGenericWaves * j) * P.KK) << 10);
+  const unsigned voff = 16 * lane;
+  const __bf16* row = P.in + (lane & 15) * P.ist + 8 * (lane >> 4);
+  bf16x8 b[RING][KP][TJ];
+  const auto fetch = [&](int s, int kk) {
+#pragma unroll
+    for (int k = 0; k < KP; ++k)
+#pragma unroll
+      for (int j = 0; j < TJ; ++j)
+        b[s][k][j] = *(const __attribute__((address_space(1))) bf16x8*)(W[k][j] + (static_cast<unsigned>(kk) << 10) + voff);
+  };
+  const auto products = [&](int s, int kk) {
+#pragma unroll
+    for (int k = 0; k < KP; ++k)
+#pragma unroll
+      for (int r = 0; r < ROWT; ++r) {
+        const bf16x8 a = *reinterpret_cast<const bf16x8*>(row + k * P.astride + 16 * r * P.ist + 32 * kk);
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) acc[k][r][j] = mfma_bf16(a, b[s][k][j], acc[k][r][j]);
+      }
+  };
+#pragma unroll
+  for (int s = 0; s < RING; ++s)
+    if (P.kbeg + s < P.kend) fetch(s, P.kbeg + s);
+  int g = P.kbeg;
+  for (; g + 2 * RING <= P.kend; g += RING) {
+#pragma unroll
+    for (int s = 0; s < RING; ++s) {
+      products(s, g + s);
+      fetch(s, g + RING + s);
+    }
+  }
+  // The last one or two rounds, the second of them short.
+#pragma unroll
+  for (int s = 0; s < RING; ++s)
+    if (g + s < P.kend) {
+      products(s, g + s);
+      if (g + RING + s < P.kend) fetch(s, g + RING + s);
+    }
+  g += RING;
+#pragma unroll
+  for (int s = 0; s < RING; ++s)
+    if (g + s < P.kend) products(s, g + s);
+}
+
+// kp actors (1..kPass) and tj tiles of the wavefront (0..TM).
+template <int ROWT, int TM>
+__device__ __forceinline__ void pass_layer(const PassLayer& P, int kp, int tj, int lane,
+                                           floatx4 (&acc)[kPass][ROWT][TM]) {
+#pragma unroll
+  for (int k = 0; k < kPass; ++k)
+#pragma unroll
+    for (int r = 0; r < ROWT; ++r)
+#pragma unroll
+      for (int j = 0; j < TM; ++j) acc[k][r][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+  static_for<TM>([&](auto ji) {
+    constexpr int TJ = ji + 1, RING = TJ <= 2 ? 4 : 2;
+    if (tj != TJ) return;
+    if (kp == 1) pass_products<ROWT, 1, TJ, RING>(P, lane, acc);
+    else if (kp == 2) pass_products<ROWT, 2, TJ, RING>(P, lane, acc);
+    else pass_products<ROWT, 3, TJ, RING>(P, lane, acc);
+  });
+}
+
+// fast_tanh of four values side by side (a dependent vector instruction waits about twice as long
+// as an independent one takes; the fences keep the compiler from making chains of them).
+__device__ __forceinline__ void tanh4(float (&x)[4]) {
+  float t[4], r[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) t[q] = -2.8853900817779268f * fabsf(x[q]);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) t[q] = __builtin_amdgcn_exp2f(t[q]);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) r[q] = 1.0f + t[q];
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) r[q] = __builtin_amdgcn_rcpf(r[q]);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) t[q] = 1.0f - t[q];
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) t[q] = t[q] * r[q];
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) x[q] = copysignf(t[q], x[q]);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -802,170 +962,407 @@ __global__ __launch_bounds__(kStreamThreads) void fused_streamed_kernel(EnvConst
   }
 }
 
+// Actors per pass of the generic schedule: kPass where their hidden rows fit the LDS, else two (which
+// every accepted shape has room for).
+__host__ __device__ inline int generic_areas(int MR, const EnvConst& C, const EnsDev& E, int st0) {
+  if (E.K <= 2) return 2;
+  return FusedLds::bytes(MR, st0, E.H + 8, C.D, C.I, kPass) <= kBatchedMaxLds ? kPass : 2;
+}
+
 // One tile (16*ROWT environments starting at tile*16*ROWT) through the steps of F, generic
 // schedule: the body of the generic kernel and of the batched persistent kernel.
-template <int ROWT, int TMAX>
+// A step is a chain of latencies (weights from L2, barriers, the serial cash recurrence), so what
+// it waits for is passed as few times as the results allow: a layer of three actors at once, the
+// trading part in one piece by rows, and the noise, market rows and trajectory stores of a
+// neighbouring step beside it on the wavefronts that it leaves idle.  On 1000 environments of 17
+// stocks, 128 units and three actors a step takes 10.5 us, against 21.1 with a layer of one actor
+// at a time, four wavefronts and the chain by phases; 24 uneven groups up to 4096 environments and
+// 400 days at 256 units 26.5 ms against 42.6.
+template <int ROWT, int TMAX, bool ROWS>
 __device__ __forceinline__ void generic_tile(const EnvConst& C, const EnvState& st, const EnsDev& E,
                                              const FusedArgs& F, int tile, unsigned char* smem) {
-  constexpr int NT = 256, MR = 16 * ROWT;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int NT = kGenericThreads, NW = kGenericWaves, MR = 16 * ROWT;
+  constexpr int kMk = 3;  // market values per thread of the wavefronts past the owners'
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int D = C.D, N = C.N, DS = D + 1;
   const int n0 = tile * MR;
   const int M = min(MR, N - n0);
   // Split first layer when the day's market tables come with the launch (F.mt, [n_steps][K][H],
   // bias included): layer 1 runs on the ke_pad per-environment entries only.
-  const int split_pad = F.mt != nullptr ? E.ke_pad : 0;
-  const int st0 = (split_pad > 0 ? split_pad : E.S_pad) + 8, sth = E.H + 8;
+  const bool split = F.mt != nullptr;
+  const int kin1 = split ? E.ke_pad : E.S_pad;
+  const int st0 = kin1 + 8, sth = E.H + 8;
+  const int areas = generic_areas(MR, C, E, st0);
+
+  const int me = wave * (MR / kOwnerWaves) + lane, n = n0 + me;
+  const bool owner = wave < kOwnerWaves && lane < MR / kOwnerWaves && me < M;
+  const int idle = tid - 64 * kOwnerWaves;  // index among the threads past the owners' wavefronts
 
   FusedLds L;
-  L.carve(smem, MR, st0, sth, D);
-  EnvPhase<NT> P{C, F, L, tid, lane, wave, n0, M, E.S_pad, st0, 1.0f / static_cast<float>(D),
+  L.carve(smem, MR, st0, sth, D, areas);
+  EnvPhase<NT> P{C, F, L, tid, lane, wave, n0, M, st0, me, 1.0f / static_cast<float>(D),
                  1.0f / static_cast<float>((D + 3) >> 2), (D + 3) >> 2};
 
   for (int i = tid; i < MR * st0; i += NT) L.x0[i] = static_cast<__bf16>(0.0f);
 
-  const bool owner = wave == 0 && lane < M;
-  const int n = n0 + lane;
-  double cash = 0.0, asset = 0.0, cumrew = 0.0;
-  P.load_state(owner, st, cash, asset, cumrew);
+  // ROWS (up to 32 stocks): the owners' wavefronts run the whole trading part, a 16-lane row per
+  // environment (row_m(q): the row's environment of set q), with the state in registers; wider
+  // environments take the chain by phases, a lane per environment, holdings in LDS.
+  const int jl = lane & 15;
+  const auto row_m = [&](int q) { return 16 * q + 4 * wave + (lane >> 4); };
+  double cash[ROWT], asset[ROWT], cumrew[ROWT];
+  int hold[ROWT][2];
+#pragma unroll
+  for (int q = 0; q < ROWT; ++q) {
+    cash[q] = asset[q] = cumrew[q] = 0.0;
+    hold[q][0] = hold[q][1] = 0;
+  }
+  if constexpr (!ROWS) {
+    P.load_state(owner, st, cash[0], asset[0], cumrew[0]);
+  } else if (wave < kOwnerWaves) {
+#pragma unroll
+    for (int q = 0; q < ROWT; ++q) {
+      const int m = row_m(q);
+      if (m >= M) continue;
+      cash[q] = st.cash[n0 + m];
+      asset[q] = st.asset[n0 + m];
+      cumrew[q] = st.cumrew[n0 + m];
+      if (jl == 0) L.env[m * DS] = static_cast<float>(cash[q] * static_cast<double>(C.cash_scale));
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const int d = jl + 16 * s;
+        if (d >= D) continue;
+        hold[q][s] = st.hold[static_cast<size_t>(d) * N + n0 + m];
+        L.env[m * DS + 1 + d] = static_cast<float>(hold[q][s]) * C.hold_scale;
+      }
+    }
+  }
 
-  P.stage_market(F.t0, false);
-  P.env_entries(owner, cash);
+  for (int d = tid; d < D; d += NT) L.pn[d] = gbl(C.close)[static_cast<size_t>(F.t0) * D + d];
+  P.stage_market(F.t0);
+  if constexpr (!ROWS) P.env_entries(owner, cash[0]);
+  P.draw(F.t0, tid, NT);
+  // The market rows of the step's new day, in registers of the threads past the owners' wavefronts;
+  // more than those hold are staged by all threads when they are needed.
+  const bool held = (1 + C.I) * D <= kMk * kIdleThreads;
+  float mk[kMk], mk_next[kMk];
+  if (held && idle >= 0) P.fetch_market(mk_next, F.t0 + 1, idle, kIdleThreads);
   __syncthreads();
-  P.assemble(nullptr, split_pad);
+  P.assemble(split);
 
   const int row_q = 4 * (lane >> 4), col_l = lane & 15;
   const int ht = E.H / 16, at = E.A_pad / 16;
-  // Layer 3's k-range slices: the wavefronts left over by its output tiles (partial tiles of
-  // sl3 * at * ROWT * 1024 bytes in the layer-1 output area).
+  // Layer 3 with fewer than four output tiles: its k range in sl3 slices (the count is part of the
+  // result's rounding); wavefront c3 + at * q3 takes slice q3 of tile c3.  The partial tiles, of
+  // sl3 * at * ROWT * 1024 bytes, meet in the actor's hidden rows.
   const int kk3 = E.H / 32;
   int sl3 = at < 4 ? min(4 / at, kk3) : 1;
   while (sl3 > 1 && sl3 * at * ROWT * 1024 > MR * sth * 2) --sl3;
+  const int c3 = wave % at, q3 = wave / at;
+  const int tiles_h = wave < ht ? (ht - wave + NW - 1) / NW : 0;
+  const int tiles_o = sl3 > 1 ? (q3 < sl3 ? 1 : 0) : wave < at ? (at - wave + NW - 1) / NW : 0;
+
+  // The trading part of step `it` by rows; entered with the means complete, left with the next state
+  // and its inputs written but not yet synchronised.
+  const auto row_step = [&](int it, bool more) {
+#pragma clang fp contract(off)
+    const int t = F.t0 + it;
+    const size_t row_base = static_cast<size_t>(it) * N + n0;
+    float z[4];
+    float he[ROWT][2], ce[ROWT];
+    const int zm = div_small(max(idle, 0), P.inv_g), zg = max(idle, 0) - zm * P.G;
+    if (wave < kOwnerWaves) {
+      int kown[ROWT][2], sold[ROWT][2];
+      double pro[2][ROWT], val[2][ROWT], v_new[ROWT];
+      BuySet B[ROWT][2];
+#pragma unroll
+      for (int q = 0; q < ROWT; ++q)
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          const int m = row_m(q), d = jl + 16 * s;
+          const bool on = m < M && d < D;
+          float act = 0.0f, p = 0.0f;
+          if (on) {
+            act = L.abar[m * DS + d];
+            if (F.sigma != 0.0f) act = act + F.sigma * L.act[m * D + d];
+            act = fminf(fmaxf(act, -1.0f), 1.0f);
+            p = L.px[d];
+            if (F.act_traj) gbl(F.act_traj)[(row_base + m) * D + d] = act;
+          }
+          const int o = on ? order_from_action(act, C.hmax_f) : 0;
+          sold[q][s] = o < 0 ? min(hold[q][s], -o) : 0;
+          hold[q][s] -= sold[q][s];
+          const double pd = static_cast<double>(p);
+          const int qd = o > 0 ? o : 0;
+          pro[s][q] = (pd * static_cast<double>(sold[q][s])) * C.one_m;
+          B[q][s].deb = (pd * static_cast<double>(qd)) * C.one_p;
+          B[q][s].c1 = pd * C.one_p;
+          B[q][s].pq = pack_pq(p, qd);
+          kown[q][s] = 0;
+        }
+      row_sums(cash, pro[0]);
+      row_sums(cash, pro[1]);
+      buy_all_seg4<ROWT>(cash, kown, lane, B, C.one_p);
+#pragma unroll
+      for (int q = 0; q < ROWT; ++q) {
+        v_new[q] = cash[q];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          const int m = row_m(q), d = jl + 16 * s;
+          const bool on = m < M && d < D;
+          hold[q][s] += kown[q][s];
+          val[s][q] = static_cast<double>(on ? L.pn[d] : 0.0f) * static_cast<double>(hold[q][s]);
+          he[q][s] = static_cast<float>(hold[q][s]) * C.hold_scale;
+          if (on && F.qty_traj) gbl(F.qty_traj)[(row_base + m) * D + d] = kown[q][s] - sold[q][s];
+        }
+      }
+      row_sums(v_new, val[0]);
+      row_sums(v_new, val[1]);
+#pragma unroll
+      for (int q = 0; q < ROWT; ++q) {
+        const double rw = (v_new[q] - asset[q]) * C.reward_scale;
+        cumrew[q] = cumrew[q] + rw;
+        asset[q] = v_new[q];
+        ce[q] = static_cast<float>(cash[q] * static_cast<double>(C.cash_scale));
+        if (jl == 0 && row_m(q) < M && F.rew_traj) gbl(F.rew_traj)[row_base + row_m(q)] = rw;
+      }
+    } else {
+      // Beside it: the next step's market rows and noise (at most one block per thread), and the
+      // stores of the last step's state rows.
+      if (more) P.fetch_market(mk_next, t + 2, idle, kIdleThreads);
+      if (more && F.sigma != 0.0f && zm < M)
+        noise_block(F.key, static_cast<uint64_t>(F.env_offset + n0 + zm), static_cast<uint64_t>(t + 1),
+                    static_cast<uint64_t>(zg), z);
+      if (F.obs_traj && it > 0)
+        P.store_states(F.obs_traj + (row_base - N) * C.S, wave - kOwnerWaves, NW - kOwnerWaves);
+    }
+    __syncthreads();
+    if (wave < kOwnerWaves) {
+#pragma unroll
+      for (int q = 0; q < ROWT; ++q) {
+        const int m = row_m(q);
+        if (m >= M) continue;
+        if (jl == 0) {
+          L.env[m * DS] = ce[q];
+          if (split) L.x0[m * st0] = static_cast<__bf16>(ce[q]);
+        }
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          const int d = jl + 16 * s;
+          if (d >= D) continue;
+          L.env[m * DS + 1 + d] = he[q][s];
+          if (split) L.x0[m * st0 + 1 + d] = static_cast<__bf16>(he[q][s]);
+        }
+      }
+    } else {
+      P.put_market(mk, idle, kIdleThreads);
+      if (more) {
+        P.put_closes(mk_next, idle, kIdleThreads);
+#pragma unroll
+        for (int j = 0; j < kMk; ++j) mk[j] = mk_next[j];
+        if (F.sigma != 0.0f && zm < M)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (4 * zg + e < D) L.act[zm * D + 4 * zg + e] = z[e];
+      }
+    }
+    if (!split) {
+      __syncthreads();
+      P.assemble(false);
+    }
+  };
 
   for (int it = 0; it < F.n_steps; ++it) {
     const int t = F.t0 + it;
     const size_t row_base = static_cast<size_t>(it) * N + n0;
     __syncthreads();
-    P.stage_market(t + 1, true);
-
-    for (int k = 0; k < E.K; ++k) {
-      const unsigned char* PA = E.base + static_cast<size_t>(k) * E.actor_stride;
-      const float* b1 = reinterpret_cast<const float*>(PA + E.off_b1);
-      const float* b2 = reinterpret_cast<const float*>(PA + E.off_b2);
-      const float* b3 = reinterpret_cast<const float*>(PA + E.off_b3);
-      const float wk = gbl(E.mix)[k];
-      // Layer 1's bias, or with the split layer the day's market share (bias included).
-      const float* b1t = split_pad > 0 ? F.mt + (static_cast<size_t>(it) * E.K + k) * E.H : b1;
-      const bf16x8* W1 = split_pad > 0
-                             ? reinterpret_cast<const bf16x8*>(E.base + E.off_w1e +
-                                                               static_cast<size_t>(k) * E.H * split_pad * 2)
-                             : reinterpret_cast<const bf16x8*>(PA + E.off_w1);
-      // Each layer's biases for the wavefront's output tiles are requested before its k loop, so
-      // that the epilogues do not wait for them (up to four tiles per wavefront; with eight the
-      // registers are short, and the epilogue reads its bias).
-      constexpr bool kPre = TMAX <= 4;
-      float bv[TMAX];
-      const float* bsrc = nullptr;
-      auto bias = [&](const float* b, int ntiles, int n) {  // n: the layer's outputs
-        bsrc = b;
-        if constexpr (kPre) {
+    if (ROWS && it > 0) {
+      // staged at the end of the step before
+    } else if (!held) {
+      P.stage_closes(t + 1);
+    } else if (idle >= 0) {
 #pragma unroll
-          for (int i = 0; i < TMAX; ++i) {
-            const int c = wave + 4 * i;
-            bv[i] = c < ntiles && 16 * c + col_l < n ? gbl(b)[16 * c + col_l] : 0.0f;
-          }
-        }
-      };
-      auto bias_of = [&](int i, int col) -> float {
-        if constexpr (kPre) return bv[i];
-        else return gbl(bsrc)[col];
-      };
-      bias(b1t, ht, E.H);
-      layer_bf16<ROWT, TMAX>(L.x0, st0, split_pad > 0 ? split_pad : E.S_pad, W1, ht, wave, lane,
-                             [&](int rt, int i, int c, floatx4 acc) {
-                               const int col = 16 * c + col_l;
-                               const float b = bias_of(i, col);
-#pragma unroll
-                               for (int q = 0; q < 4; ++q)
-                                 L.x1[(rt * 16 + row_q + q) * sth + col] = static_cast<__bf16>(fast_tanh(acc[q] + b));
-                             });
-      bias(b2, ht, E.H);
-      __syncthreads();
-      layer_bf16<ROWT, TMAX>(L.x1, sth, E.H, reinterpret_cast<const bf16x8*>(PA + E.off_w2), ht, wave, lane,
-                             [&](int rt, int i, int c, floatx4 acc) {
-                               const int col = 16 * c + col_l;
-                               const float b = bias_of(i, col);
-#pragma unroll
-                               for (int q = 0; q < 4; ++q)
-                                 L.x2[(rt * 16 + row_q + q) * sth + col] = static_cast<__bf16>(fast_tanh(acc[q] + b));
-                             });
-      bias(b3, at, E.A);
-      __syncthreads();
-      auto out3 = [&](int rt, int i, int c, floatx4 acc) {
-        const int col = 16 * c + col_l;
-        if (col >= E.A) return;
-        const float b = bias_of(i, col);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          float* dst = &L.abar[(rt * 16 + row_q + q) * DS + col];
-          const float v = wk * fast_tanh(acc[q] + b);
-          *dst = (k == 0) ? v : (*dst + v);
-        }
-      };
-      const bf16x8* W3 = reinterpret_cast<const bf16x8*>(PA + E.off_w3);
-      if (sl3 == 1) {
-        layer_bf16<ROWT, TMAX>(L.x2, sth, E.H, W3, at, wave, lane, out3);
-      } else {
-        // Fewer output tiles than wavefronts: the k range is split over them, the partial tiles
-        // meet in LDS over layer 1's outputs (read by now) and are summed in slice order.
-        floatx4* part = reinterpret_cast<floatx4*>(L.x1);  // [sl3][at][ROWT][64]
-        const int c3 = wave % at, q3 = wave / at;
-        auto e3 = [&](int rt, int, int, floatx4 acc) { part[((q3 * at + c3) * ROWT + rt) * 64 + lane] = acc; };
-        if (q3 < sl3)
-          mlp_layer<kBF16, 1, ROWT, 1, decltype(e3), 4>(L.x2, sth, E.H, W3, at, c3, lane, e3, q3 * kk3 / sl3,
-                                                        (q3 + 1) * kk3 / sl3);
-        __syncthreads();
-        if (wave < at) {
-#pragma unroll
-          for (int rt = 0; rt < ROWT; ++rt) {
-            floatx4 acc = part[(wave * ROWT + rt) * 64 + lane];
-            for (int q = 1; q < sl3; ++q) {
-              const floatx4 p = part[((q * at + wave) * ROWT + rt) * 64 + lane];
-#pragma unroll
-              for (int r = 0; r < 4; ++r) acc[r] = acc[r] + p[r];
-            }
-            out3(rt, 0, wave, acc);  // tile c = wave: slot 0 of the wavefront's biases
-          }
-        }
-      }
-      __syncthreads();
+      for (int j = 0; j < kMk; ++j) mk[j] = mk_next[j];
+      P.put_closes(mk, idle, kIdleThreads);
     }
 
-    P.actions(t, row_base);
-    __syncthreads();
-    const double rwd = P.chain(owner, cash, asset, cumrew);
-    if (owner && F.rew_traj) gbl(F.rew_traj)[static_cast<size_t>(it) * N + n] = rwd;
-    __syncthreads();
-    P.quantities(row_base);
-    P.assemble(F.obs_traj ? F.obs_traj + row_base * C.S : nullptr, split_pad);
-  }
+    for (int k0 = 0; k0 < E.K; k0 += areas) {
+      const int kp = min(areas, E.K - k0);
+      const unsigned char* PA = E.base + static_cast<size_t>(k0) * E.actor_stride;
+      floatx4 acc[kPass][ROWT][TMAX];
+#pragma unroll 1
+      for (int l = 0; l < 3; ++l) {
+        const bool own3 = l == 2 && sl3 > 1;
+        const int tj = l < 2 ? tiles_h : tiles_o;
+        // Biases of the wavefront's tiles (of layer 1: with the split layer the day's market share,
+        // bias included), requested before the weights.
+        const unsigned char* bias = PA + (l == 0 ? E.off_b1 : l == 1 ? E.off_b2 : E.off_b3);
+        size_t bstride = E.actor_stride;
+        PassLayer Q{PA + (l == 0 ? E.off_w1 : l == 1 ? E.off_w2 : E.off_w3), E.actor_stride, L.x1, MR * sth, sth,
+                    E.H / 32, wave, 0, E.H / 32};
+        if (l == 0) {
+          Q.in = L.x0;
+          Q.astride = 0;
+          Q.ist = st0;
+          Q.KK = Q.kend = kin1 / 32;
+          if (split) {
+            Q.wstride = static_cast<size_t>(E.H) * kin1 * 2;
+            Q.w = E.base + E.off_w1e + k0 * Q.wstride;
+            bias = reinterpret_cast<const unsigned char*>(F.mt + (static_cast<size_t>(it) * E.K + k0) * E.H);
+            bstride = sizeof(float) * E.H;
+          }
+        } else if (own3) {
+          Q.c0 = c3;
+          Q.kbeg = q3 * kk3 / sl3;
+          Q.kend = (q3 + 1) * kk3 / sl3;
+        }
+        float bv[kPass][TMAX];
+        const int cols = l < 2 ? E.H : E.A;
+#pragma unroll
+        for (int k = 0; k < kPass; ++k)
+#pragma unroll
+          for (int j = 0; j < TMAX; ++j) {
+            // Sliced: wavefront c + at * (row tile) completes tile c.
+            const int col = 16 * (own3 ? c3 : wave + NW * j) + col_l;
+            bv[k][j] = 0.0f;
+            if (k < kp && col < cols) bv[k][j] = gbl(reinterpret_cast<const float*>(bias + k * bstride))[col];
+          }
+        pass_layer<ROWT>(Q, kp, tj, lane, acc);
+        if (l > 0) __syncthreads();  // the hidden rows are written over
+        if (l < 2) {
+#pragma unroll
+          for (int k = 0; k < kPass; ++k)
+#pragma unroll
+            for (int j = 0; j < TMAX; ++j)
+              if (k < kp && j < tj)
+#pragma unroll
+                for (int r = 0; r < ROWT; ++r) {
+                  float x[4];
+#pragma unroll
+                  for (int q = 0; q < 4; ++q) x[q] = acc[k][r][j][q] + bv[k][j];
+                  tanh4(x);
+                  __bf16* o = L.x1 + (k * MR + r * 16 + row_q) * sth + 16 * (wave + NW * j) + col_l;
+#pragma unroll
+                  for (int q = 0; q < 4; ++q) o[q * sth] = static_cast<__bf16>(x[q]);
+                }
+          __syncthreads();
+          continue;
+        }
+        // a_bar += w_k * tanh(acc_k + bias), in actor order.
+        const auto mean = [&](int r, int c, int j, auto value) {
+          const int col = 16 * c + col_l;
+          float sum[4];
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            sum[q] = k0 > 0 && col < E.A ? L.abar[(r * 16 + row_q + q) * DS + col] : 0.0f;
+#pragma unroll
+          for (int k = 0; k < kPass; ++k)
+            if (k < kp) {
+              const floatx4 v = value(k);
+              const float wk = gbl(E.mix)[k0 + k];
+              float x[4];
+#pragma unroll
+              for (int q = 0; q < 4; ++q) x[q] = v[q] + bv[k][j];
+              tanh4(x);
+#pragma unroll
+              for (int q = 0; q < 4; ++q) sum[q] = k0 + k == 0 ? wk * x[q] : sum[q] + wk * x[q];
+            }
+          if (col < E.A)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) L.abar[(r * 16 + row_q + q) * DS + col] = sum[q];
+        };
+        if (sl3 == 1) {
+#pragma unroll
+          for (int j = 0; j < TMAX; ++j)
+            if (j < tj)
+#pragma unroll
+              for (int r = 0; r < ROWT; ++r) mean(r, wave + NW * j, j, [&](int k) { return acc[k][r][j]; });
+        } else {
+          // [actor][sl3][at][ROWT][64], an actor's tiles in its hidden rows.
+          const int area = MR * sth / 8;
+          floatx4* part = reinterpret_cast<floatx4*>(L.x1);
+          if (tj > 0)
+#pragma unroll
+            for (int k = 0; k < kPass; ++k)
+              if (k < kp)
+#pragma unroll
+                for (int r = 0; r < ROWT; ++r) part[k * area + ((q3 * at + c3) * ROWT + r) * 64 + lane] = acc[k][r][0];
+          __syncthreads();
+          if (wave < at * ROWT)
+            mean(q3, c3, 0, [&](int k) {
+              floatx4 v = part[k * area + (c3 * ROWT + q3) * 64 + lane];
+              for (int q = 1; q < sl3; ++q) {
+                const floatx4 p = part[k * area + ((q * at + c3) * ROWT + q3) * 64 + lane];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = v[e] + p[e];
+              }
+              return v;
+            });
+        }
+        __syncthreads();
+      }
+    }
 
-  P.store_state(owner, st, cash, asset, cumrew);
+    const bool more = it + 1 < F.n_steps;
+    if constexpr (ROWS) {
+      row_step(it, more);
+    } else {
+      P.actions(row_base);
+      __syncthreads();
+      const double rwd = P.chain(
+          owner, cash[0], asset[0], cumrew[0],
+          [&]() {
+            // Beside the cash recurrence: the next step's market rows and noise, and the stores of the
+            // last step's state rows (the step's own would be waited for by its next loads).
+            if (held && more) P.fetch_market(mk_next, t + 2, idle, kIdleThreads);
+            if (more) P.draw(t + 1, idle, kIdleThreads);
+            if (F.obs_traj && it > 0)
+              P.store_states(F.obs_traj + (row_base - N) * C.S, wave - kOwnerWaves, NW - kOwnerWaves);
+          },
+          [&]() {
+            if (!held) P.stage_market(t + 1);
+            else if (idle >= 0) P.put_market(mk, idle, kIdleThreads);
+          });
+      if (owner && F.rew_traj) gbl(F.rew_traj)[static_cast<size_t>(it) * N + n] = rwd;
+      __syncthreads();
+      P.quantities(row_base);
+      P.assemble(split);
+    }
+  }
+  if constexpr (ROWS) __syncthreads();
+  if (F.obs_traj && F.n_steps > 0)
+    P.store_states(F.obs_traj + (static_cast<size_t>(F.n_steps - 1) * N + n0) * C.S, wave, NW);
+
+  if constexpr (!ROWS) {
+    P.store_state(owner, st, cash[0], asset[0], cumrew[0]);
+  } else if (wave < kOwnerWaves) {
+#pragma unroll
+    for (int q = 0; q < ROWT; ++q) {
+      const int m = row_m(q);
+      if (m >= M) continue;
+      if (jl == 0) {
+        st.cash[n0 + m] = cash[q];
+        st.asset[n0 + m] = asset[q];
+        st.cumrew[n0 + m] = cumrew[q];
+      }
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+        if (jl + 16 * s < D) st.hold[static_cast<size_t>(jl + 16 * s) * N + n0 + m] = hold[q][s];
+    }
+  }
 }
 
-template <int ROWT, int TMAX>
-__global__ __launch_bounds__(256) void fused_generic_kernel(EnvConst C, EnvState st, EnsDev E,
+template <int ROWT, int TMAX, bool ROWS>
+__global__ __launch_bounds__(kGenericThreads) void fused_generic_kernel(EnvConst C, EnvState st, EnsDev E,
                                                             FusedArgs F) {
   extern __shared__ __align__(16) unsigned char smem[];
-  generic_tile<ROWT, TMAX>(C, st, E, F, blockIdx.x, smem);
+  generic_tile<ROWT, TMAX, ROWS>(C, st, E, F, blockIdx.x, smem);
 }
 
 // Batched persistent kernel (uneven groups): every workgroup takes work items -- (group, tile)
 // pairs, ordered by decreasing cost -- from a counter until none is left, and runs each item's
 // steps with the generic schedule.  The item counter is reset by zero_counter_kernel before each
 // launch (a kernel, not a memset, so that the pair can be captured in a graph).
-constexpr size_t kBatchedMaxLds = 160 * 1024 - 256;  // the kernel's own item slot takes a little
-
 struct GroupDesc {
   EnvConst C;
   EnvState st;
@@ -974,7 +1371,7 @@ struct GroupDesc {
 };
 
 template <int ROWT, int TMAX>
-__global__ __launch_bounds__(256) void fused_batched_kernel(const GroupDesc* __restrict__ groups,
+__global__ __launch_bounds__(kGenericThreads) void fused_batched_kernel(const GroupDesc* __restrict__ groups,
                                                             const int2* __restrict__ items, int n_items,
                                                             int* __restrict__ counter) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -982,12 +1379,26 @@ __global__ __launch_bounds__(256) void fused_batched_kernel(const GroupDesc* __r
   for (;;) {
     if (threadIdx.x == 0) s_item = atomicAdd(counter, 1);
     __syncthreads();
-    const int item = s_item;
+    const int item = __builtin_amdgcn_readfirstlane(s_item);
     __syncthreads();
     if (item >= n_items) break;
-    const int2 gt = items[item];
-    const GroupDesc G = groups[gt.x];
-    if (G.F.n_steps > 0) generic_tile<ROWT, TMAX>(G.C, G.st, G.E, G.F, gt.y, smem);
+    // The lists are constant for the launch: read as such, the group's descriptor sits in scalar
+    // registers.
+    typedef const __attribute__((address_space(4))) unsigned* cptr;
+    static_assert(sizeof(GroupDesc) % 4 == 0, "copied by words");
+    const cptr gt = (cptr)(items + item);
+    const int tile = gt[1];
+    const cptr src = (cptr)(groups + gt[0]);
+    unsigned w[sizeof(GroupDesc) / 4];
+#pragma unroll
+    for (size_t i = 0; i < sizeof(GroupDesc) / 4; ++i) w[i] = src[i];
+    GroupDesc G;
+    __builtin_memcpy(&G, w, sizeof(GroupDesc));
+    if (G.F.n_steps <= 0) continue;
+    if (G.C.D <= 32)
+      generic_tile<ROWT, TMAX, true>(G.C, G.st, G.E, G.F, tile, smem);
+    else
+      generic_tile<ROWT, TMAX, false>(G.C, G.st, G.E, G.F, tile, smem);
   }
 }
 
@@ -1007,16 +1418,17 @@ hipError_t go(Kern kern, int grid, int threads, size_t lds, hipStream_t stream, 
 
 hipError_t launch_generic(const EnvConst& C, const EnvState& st, const EnsDev& E, const FusedArgs& F,
                           hipStream_t stream, std::string* why) {
-  const size_t lds = FusedLds::bytes(16, E.S_pad + 8, E.H + 8, C.D, C.I);
+  const size_t lds = FusedLds::bytes(16, E.S_pad + 8, E.H + 8, C.D, C.I, generic_areas(16, C, E, E.S_pad + 8));
   if (lds > 160 * 1024) {
     *why = "fused rollout: state and hidden sizes exceed the LDS budget";
     return hipSuccess;
   }
   const int grid = (C.N + 15) / 16;
-  const int tiles_per_wave = (E.H / 16 + 3) / 4;
-  if (tiles_per_wave <= 2) return go(fused_generic_kernel<1, 2>, grid, 256, lds, stream, C, st, E, F);
-  if (tiles_per_wave <= 4) return go(fused_generic_kernel<1, 4>, grid, 256, lds, stream, C, st, E, F);
-  return go(fused_generic_kernel<1, 8>, grid, 256, lds, stream, C, st, E, F);
+  if (E.H <= 2 * 16 * kGenericWaves)
+    return go(C.D <= 32 ? fused_generic_kernel<1, 2, true> : fused_generic_kernel<1, 2, false>, grid, kGenericThreads,
+              lds, stream, C, st, E, F);
+  return go(C.D <= 32 ? fused_generic_kernel<1, 4, true> : fused_generic_kernel<1, 4, false>, grid, kGenericThreads,
+            lds, stream, C, st, E, F);
 }
 
 // Ring depth (k-steps of weight fragments in flight) by row tiles: the register budget of five
@@ -1099,7 +1511,8 @@ bool fused_streamed_shape(const EnvConst& C, const EnsDev& E) {
 }
 
 size_t batched_lds_bytes(int rows, const EnvConst& C, const EnsDev& E) {
-  return FusedLds::bytes(rows, (E.split_a > 0 ? E.ke_pad : E.S_pad) + 8, E.H + 8, C.D, C.I);
+  const int st0 = (E.split_a > 0 ? E.ke_pad : E.S_pad) + 8;
+  return FusedLds::bytes(rows, st0, E.H + 8, C.D, C.I, generic_areas(rows, C, E, st0));
 }
 
 hipError_t launch_market_table(const EnvConst& C, const EnsDev& E, int t, int n, float* mt, hipStream_t stream) {
@@ -1122,8 +1535,8 @@ void batched_group_desc(const EnvConst& C, const EnvState& st, const EnsDev& E, 
 }
 
 hipError_t prepare_batched(size_t lds) {
-  for (const void* k : {reinterpret_cast<const void*>(fused_batched_kernel<1, 4>),
-                        reinterpret_cast<const void*>(fused_batched_kernel<2, 4>)}) {
+  for (const void* k : {reinterpret_cast<const void*>(fused_batched_kernel<1, 2>),
+                        reinterpret_cast<const void*>(fused_batched_kernel<2, 2>)}) {
     const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
     if (e != hipSuccess) return e;
   }
@@ -1139,9 +1552,9 @@ hipError_t launch_batched(int rows, int blocks, size_t lds, const void* groups, 
   const GroupDesc* g = static_cast<const GroupDesc*>(groups);
   const int2* it = reinterpret_cast<const int2*>(items);
   if (rows == 32)
-    hipLaunchKernelGGL((fused_batched_kernel<2, 4>), dim3(blocks), dim3(256), lds, stream, g, it, n_items, counter);
+    hipLaunchKernelGGL((fused_batched_kernel<2, 2>), dim3(blocks), dim3(kGenericThreads), lds, stream, g, it, n_items, counter);
   else
-    hipLaunchKernelGGL((fused_batched_kernel<1, 4>), dim3(blocks), dim3(256), lds, stream, g, it, n_items, counter);
+    hipLaunchKernelGGL((fused_batched_kernel<1, 2>), dim3(blocks), dim3(kGenericThreads), lds, stream, g, it, n_items, counter);
   return hipGetLastError();
 }
 
