@@ -81,108 +81,4 @@ __device__ __forceinline__ floatx4 mfma_bf16(bf16x8 a, bf16x8 b, floatx4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-// One layer for RT row tiles of 16 and the wavefront's column tiles c = wave, wave + NW, ...
-// (< ntiles; NW wavefronts per workgroup).  sin: LDS tile [16 RT][in_stride] holding kin_pad
-// valid (zero-padded) columns.  Calls epi(r, i, c, acc) for every (row tile r, column tile c) the
-// wave owns.  Each B-operand fragment serves all RT row tiles; the fragments of the next RING
-// k-steps are in flight while the current k-step's MFMAs run.  [kbeg, kend) restricts the sum to
-// those k-steps (16 k for float32, 32 for bfloat16; kend < 0: to the end).
-// The bfloat16 weights are read through a global-address-space pointer: a pointer that reached
-// the kernel through memory (the batched form's group table) would otherwise be read with flat
-// loads, which also count on the LDS counter, so that each wait for an activation fragment in
-// LDS would wait for the weight prefetch as well.
-template <int DT, int TMAX, int RT, int NW, class Epi, int RING = 4>
-__device__ __forceinline__ void mlp_layer(const typename MT<DT>::act_t* sin, int in_stride,
-                                          int kin_pad, const void* wp, int ntiles, int wave,
-                                          int lane, Epi epi, int kbeg = 0, int kend = -1) {
-  floatx4 acc[RT][TMAX];
-#pragma unroll
-  for (int r = 0; r < RT; ++r)
-#pragma unroll
-    for (int i = 0; i < TMAX; ++i) acc[r][i] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-  const int row = lane & 15, grp = lane >> 4;
-  if constexpr (DT == kF32) {
-    const float4* W = static_cast<const float4*>(wp);
-    const int KQ = kin_pad / 16, K1 = kend < 0 ? KQ : min(kend, KQ);
-    float4 ring[RING][TMAX];
-    auto fetch = [&](float4 (&dst)[TMAX], int kq) {
-#pragma unroll
-      for (int i = 0; i < TMAX; ++i) {
-        const int c = wave + NW * i;
-        if (c < ntiles && kq < K1) dst[i] = W[(static_cast<size_t>(c) * KQ + kq) * 64 + lane];
-      }
-    };
-#pragma unroll
-    for (int j = 0; j < RING; ++j) fetch(ring[j], kbeg + j);
-    for (int kq0 = kbeg; kq0 < K1; kq0 += RING) {
-#pragma unroll
-      for (int j = 0; j < RING; ++j) {
-        const int kq = kq0 + j;
-        if (kq < K1) {
-          float4 b[TMAX];
-#pragma unroll
-          for (int i = 0; i < TMAX; ++i) b[i] = ring[j][i];
-          fetch(ring[j], kq + RING);
-          float a[RT][4];
-#pragma unroll
-          for (int r = 0; r < RT; ++r)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) a[r][e] = sin[(16 * r + row) * in_stride + 16 * kq + 4 * e + grp];
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-#pragma unroll
-            for (int i = 0; i < TMAX; ++i) {
-              if (wave + NW * i < ntiles) {
-                const float bv = e == 0 ? b[i].x : e == 1 ? b[i].y : e == 2 ? b[i].z : b[i].w;
-#pragma unroll
-                for (int r = 0; r < RT; ++r) acc[r][i] = mfma_f32(a[r][e], bv, acc[r][i]);
-              }
-            }
-        }
-      }
-    }
-  } else {
-    const __attribute__((address_space(1))) bf16x8* W = (const __attribute__((address_space(1))) bf16x8*)wp;
-    const int KK = kin_pad / 32, K1 = kend < 0 ? KK : min(kend, KK);
-    bf16x8 ring[RING][TMAX];
-    auto fetch = [&](bf16x8 (&dst)[TMAX], int kk) {
-#pragma unroll
-      for (int i = 0; i < TMAX; ++i) {
-        const int c = wave + NW * i;
-        if (c < ntiles && kk < K1) dst[i] = W[(static_cast<size_t>(c) * KK + kk) * 64 + lane];
-      }
-    };
-#pragma unroll
-    for (int j = 0; j < RING; ++j) fetch(ring[j], kbeg + j);
-    for (int kk0 = kbeg; kk0 < K1; kk0 += RING) {
-#pragma unroll
-      for (int j = 0; j < RING; ++j) {
-        const int kk = kk0 + j;
-        if (kk < K1) {
-          bf16x8 b[TMAX];
-#pragma unroll
-          for (int i = 0; i < TMAX; ++i) b[i] = ring[j][i];
-          fetch(ring[j], kk + RING);
-          bf16x8 a[RT];
-#pragma unroll
-          for (int r = 0; r < RT; ++r)
-            a[r] = *reinterpret_cast<const bf16x8*>(sin + (16 * r + row) * in_stride + 32 * kk + 8 * grp);
-#pragma unroll
-          for (int i = 0; i < TMAX; ++i)
-            if (wave + NW * i < ntiles)
-#pragma unroll
-              for (int r = 0; r < RT; ++r) acc[r][i] = mfma_bf16(a[r], b[i], acc[r][i]);
-        }
-      }
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < RT; ++r)
-#pragma unroll
-    for (int i = 0; i < TMAX; ++i) {
-      const int c = wave + NW * i;
-      if (c < ntiles) epi(r, i, c, acc[r][i]);
-    }
-}
-
 }  // namespace fm
