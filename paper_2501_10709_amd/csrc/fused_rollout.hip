@@ -338,14 +338,16 @@ __device__ __forceinline__ void pass_products(const PassLayer& P, int lane, floa
       }
   };
 #pragma unroll
-  for (int s = 0; s < RING; ++s)
-    if (P.kbeg + s < P.kend) fetch(s, P.kbeg + s);
+  for (int s = 0; s < RING; ++s) fetch(s, min(P.kbeg + s, P.kend - 1));
   int g = P.kbeg;
   for (; g + 2 * RING <= P.kend; g += RING) {
 #pragma unroll
     for (int s = 0; s < RING; ++s) {
       products(s, g + s);
       fetch(s, g + RING + s);
+      // Keeps the requests here (only LDS reads and scalar or vector arithmetic may move past):
+      // otherwise a round's requests sink to its end, and the next round waits for them.
+      __builtin_amdgcn_sched_barrier(0x106);
     }
   }
   // The last one or two rounds, the second of them short.
@@ -975,9 +977,9 @@ __host__ __device__ inline int generic_areas(int MR, const EnvConst& C, const En
 // it waits for is passed as few times as the results allow: a layer of three actors at once, the
 // trading part in one piece by rows, and the noise, market rows and trajectory stores of a
 // neighbouring step beside it on the wavefronts that it leaves idle.  On 1000 environments of 17
-// stocks, 128 units and three actors a step takes 10.5 us, against 21.1 with a layer of one actor
+// stocks, 128 units and three actors a step takes 10.4 us, against 21.1 with a layer of one actor
 // at a time, four wavefronts and the chain by phases; 24 uneven groups up to 4096 environments and
-// 400 days at 256 units 26.5 ms against 42.6.
+// 400 days at 256 units 26.0 ms against 42.6.
 template <int ROWT, int TMAX, bool ROWS>
 __device__ __forceinline__ void generic_tile(const EnvConst& C, const EnvState& st, const EnsDev& E,
                                              const FusedArgs& F, int tile, unsigned char* smem) {
