@@ -36,6 +36,18 @@ constexpr uint64_t kPhiloxM1 = 0xCA5A826395121157ull;
 constexpr uint64_t kPhiloxW0 = 0x9E3779B97F4A7C15ull;  // golden ratio
 constexpr uint64_t kPhiloxW1 = 0xBB67AE8584CAA73Bull;  // sqrt(3) - 1
 
+// The 128-bit product m * x from four 32 x 32 + 64 bit multiply-adds (the compiler forms the high
+// and the low half apart, with twice the multiplications).
+__device__ __forceinline__ void mul_wide(uint64_t m, uint64_t x, uint64_t& hi, uint64_t& lo) {
+  const uint32_t m0 = static_cast<uint32_t>(m), m1 = static_cast<uint32_t>(m >> 32);
+  const uint32_t x0 = static_cast<uint32_t>(x), x1 = static_cast<uint32_t>(x >> 32);
+  const uint64_t p0 = static_cast<uint64_t>(m0) * x0;
+  const uint64_t p1 = static_cast<uint64_t>(m0) * x1 + (p0 >> 32);
+  const uint64_t p2 = static_cast<uint64_t>(m1) * x0 + static_cast<uint32_t>(p1);
+  hi = static_cast<uint64_t>(m1) * x1 + (p1 >> 32) + (p2 >> 32);
+  lo = (p2 << 32) | static_cast<uint32_t>(p0);
+}
+
 __device__ __forceinline__ void philox4x64_10(uint64_t& c0, uint64_t& c1, uint64_t& c2,
                                               uint64_t& c3, uint64_t k0, uint64_t k1) {
 #pragma unroll
@@ -44,8 +56,9 @@ __device__ __forceinline__ void philox4x64_10(uint64_t& c0, uint64_t& c1, uint64
       k0 += kPhiloxW0;
       k1 += kPhiloxW1;
     }
-    const uint64_t hi0 = __umul64hi(kPhiloxM0, c0), lo0 = kPhiloxM0 * c0;
-    const uint64_t hi1 = __umul64hi(kPhiloxM1, c2), lo1 = kPhiloxM1 * c2;
+    uint64_t hi0, lo0, hi1, lo1;
+    mul_wide(kPhiloxM0, c0, hi0, lo0);
+    mul_wide(kPhiloxM1, c2, hi1, lo1);
     const uint64_t n0 = hi1 ^ c1 ^ k0;
     const uint64_t n2 = hi0 ^ c3 ^ k1;
     c0 = n0;

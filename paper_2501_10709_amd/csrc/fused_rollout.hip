@@ -515,22 +515,20 @@ void market_table_kernel(EnvConst C, EnsDev E, int t0, int n_days, float* __rest
   }
 }
 
-__global__ void noise_chunk_kernel(uint64_t key, int64_t env_offset, int t0, int n_days, int N, int D,
-                                   float* __restrict__ eps) {
-  const int G = (D + 3) >> 2;
-  const size_t total = static_cast<size_t>(n_days) * N * G;
-  const size_t i = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= total) return;
-  const int g = static_cast<int>(i % G);
-  const size_t rest = i / G;
-  const int n = static_cast<int>(rest % N);
-  const int c = static_cast<int>(rest / N);
+// Day blockIdx.y of the chunk, block i of its N * G noise blocks per thread.  Bound by the
+// generator's multiplications.
+__global__ __launch_bounds__(256) void noise_chunk_kernel(uint64_t key, int64_t env_offset, int t0, int N, int D,
+                                                          float* __restrict__ eps) {
+  const unsigned G = (D + 3) >> 2;
+  const unsigned i = blockIdx.x * 256u + threadIdx.x, c = blockIdx.y;
+  const unsigned n = i / G, g = i - n * G;
+  if (n >= static_cast<unsigned>(N)) return;
   float z[4];
   noise_block(key, static_cast<uint64_t>(env_offset + n), static_cast<uint64_t>(t0 + c), static_cast<uint64_t>(g), z);
   float* row = eps + (static_cast<size_t>(c) * N + n) * D;
 #pragma unroll
   for (int r = 0; r < 4; ++r)
-    if (4 * g + r < D) row[4 * g + r] = z[r];
+    if (static_cast<int>(4 * g + r) < D) row[4 * g + r] = z[r];
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1496,9 +1494,9 @@ hipError_t launch_chunk_inputs(const EnvConst& C, const EnsDev& E, int t, int n,
                      sizeof(float) * kMtDays * mt_row(Fm), stream, C, E, t, n, mt_chunk);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess || sigma == 0.0f) return err;
-  const size_t total = static_cast<size_t>(n) * C.N * ((C.D + 3) / 4);
-  hipLaunchKernelGGL(noise_chunk_kernel, dim3(static_cast<unsigned>((total + 255) / 256)), dim3(256), 0, stream, key,
-                     env_offset, t, n, C.N, C.D, eps_chunk);
+  const size_t per_day = static_cast<size_t>(C.N) * ((C.D + 3) / 4);
+  hipLaunchKernelGGL(noise_chunk_kernel, dim3(static_cast<unsigned>((per_day + 255) / 256), n), dim3(256), 0, stream, key,
+                     env_offset, t, C.N, C.D, eps_chunk);
   return hipGetLastError();
 }
 
