@@ -29,7 +29,7 @@ struct FusedArgs {
   float* act_traj;
   double* rew_traj;
   int* qty_traj;
-  const float* eps;  // streamed and resident schedules: the chunk's noise [n_steps][N][D]
+  const float* eps;  // streamed and resident schedules: the launch's noise [n_steps][N][D] (may be act_traj)
   const float* mt;   // streamed and resident schedules: the chunk's layer-1 market shares [n_steps][K][H]
   int tile_envs = 0; // streamed and resident schedules: environments per workgroup
 };
@@ -52,11 +52,46 @@ bool fused_streamed_shape(const EnvConst& C, const EnsDev& E);
 // True when the resident schedule (weights held on chip) handles them.
 bool fused_resident_shape(const EnvConst& C, const EnsDev& E);
 
-// The per-chunk inputs of the streamed and resident schedules, for days t .. t+n-1: the market
-// table mt[c][k][j] (actor k's layer-1 share of day t+c's market entries, bias included) and,
-// when sigma != 0, the noise eps[c][n][d].
-hipError_t launch_chunk_inputs(const EnvConst& C, const EnsDev& E, int t, int n, float sigma, uint64_t key,
-                               int64_t env_offset, float* eps_chunk, float* mt_chunk, hipStream_t stream);
+// The market table mt[c][k][j] of days t .. t+n-1 (actor k's layer-1 share of day t+c's market
+// entries, bias included), for ensembles that split their first layer.
+hipError_t launch_market_table(const EnvConst& C, const EnsDev& E, int t, int n, float* mt, hipStream_t stream);
+// The noise eps[c][n][d] of days t .. t+n-1.
+hipError_t launch_noise(const EnvConst& C, int t, int n, uint64_t key, int64_t env_offset, float* eps, hipStream_t stream);
+
+// Runs F's steps as launches of as many days as their inputs have room for: launch(Fc) per span of
+// days, after its market table and noise.  The table's scratch holds kFusedChunk days of the largest
+// ensemble, which is more days of a smaller one; the noise goes into the rows that the actions are
+// stored to, if they are (a kernel reads an environment's noise of a day before it writes its actions
+// there, and reads no other's), else through kFusedChunk days of scratch.  So a rollout of 252 days
+// that stores its actions is one launch of each kind and not four (each sets up the weights anew).
+template <class Launch>
+hipError_t launch_spans(const EnvConst& C, const EnsDev& E, const FusedArgs& F, float* eps_chunk, float* mt_chunk,
+                        hipStream_t stream, Launch launch) {
+  const size_t N = C.N, D = C.D, S = C.S;
+  const int table_days = static_cast<int>(fused_table_floats() / (static_cast<size_t>(E.K) * E.H));
+  // Without noise too: the streamed kernel reads its rows (and leaves them unused) at any sigma.
+  const bool scratch = !F.act_traj;
+  const int days = scratch && kFusedChunk < table_days ? kFusedChunk : table_days;
+  for (int i = 0; i < F.n_steps; i += days) {
+    const int n = F.n_steps - i < days ? F.n_steps - i : days;
+    FusedArgs Fc = F;
+    Fc.t0 = F.t0 + i;
+    Fc.n_steps = n;
+    Fc.mt = mt_chunk;
+    Fc.obs_traj = F.obs_traj ? F.obs_traj + i * N * S : nullptr;
+    Fc.act_traj = F.act_traj ? F.act_traj + i * N * D : nullptr;
+    Fc.rew_traj = F.rew_traj ? F.rew_traj + i * N : nullptr;
+    Fc.qty_traj = F.qty_traj ? F.qty_traj + i * N * D : nullptr;
+    float* eps = scratch ? eps_chunk : Fc.act_traj;
+    Fc.eps = eps;
+    hipError_t err = launch_market_table(C, E, Fc.t0, n, mt_chunk, stream);
+    if (err == hipSuccess && F.sigma != 0.0f) err = launch_noise(C, Fc.t0, n, F.key, F.env_offset, eps, stream);
+    if (err == hipSuccess) err = launch(Fc);
+    if (err != hipSuccess) return err;
+  }
+  return hipSuccess;
+}
+
 // The resident schedule over F's steps, chunk by chunk (fused_resident.hip).
 hipError_t launch_resident(const EnvConst& C, const EnvState& st, const EnsDev& E, FusedArgs F, float* eps_chunk,
                            float* mt_chunk, hipStream_t stream);
@@ -85,9 +120,6 @@ size_t batched_group_desc_bytes();
 void batched_group_desc(const EnvConst& C, const EnvState& st, const EnsDev& E, int t0, int n_steps, float sigma,
                         uint64_t key, int64_t env_offset, float* obs_traj, float* act_traj, double* rew_traj,
                         int* qty_traj, const float* mt, void* out);
-// The market table mt[c][k][j] of days t .. t+n-1 (actor k's layer-1 share of day t+c's market
-// entries, bias included), for ensembles that split their first layer.
-hipError_t launch_market_table(const EnvConst& C, const EnsDev& E, int t, int n, float* mt, hipStream_t stream);
 // The batched kernels' dynamic LDS limit: raised to lds (<= batched_max_lds()) outside any
 // stream capture.
 size_t batched_max_lds();

@@ -567,36 +567,18 @@ bool fused_resident_shape(const EnvConst& C, const EnsDev& E) {
   return fused_streamed_shape(C, E) && C.D <= 31 && E.ke_pad == 32 && (2 + C.I) * C.D <= kRIn;
 }
 
-// Per chunk of at most kFusedChunk steps: the chunk's market table and noise, then the resident
-// kernel for the chunk's steps.
+// The resident kernel over the rollout's spans of days.
 hipError_t launch_resident(const EnvConst& C, const EnvState& st, const EnsDev& E, FusedArgs F, float* eps_chunk,
                            float* mt_chunk, hipStream_t stream) {
   if (F.tile_envs < 1 || F.tile_envs > kResRows) return hipErrorInvalidValue;
   hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(fused_resident_kernel),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(RLds::total));
   if (err != hipSuccess) return err;
-  const int t_end = F.t0 + F.n_steps;
-  const size_t N = C.N, D = C.D, S = C.S;
   const int grid = (C.N + F.tile_envs - 1) / F.tile_envs;
-  for (int t = F.t0; t < t_end; t += kFusedChunk) {
-    const int n = t_end - t < kFusedChunk ? t_end - t : kFusedChunk;
-    const size_t i0 = static_cast<size_t>(t - F.t0);
-    err = launch_chunk_inputs(C, E, t, n, F.sigma, F.key, F.env_offset, eps_chunk, mt_chunk, stream);
-    if (err != hipSuccess) return err;
-    FusedArgs Fc = F;
-    Fc.t0 = t;
-    Fc.n_steps = n;
-    Fc.eps = eps_chunk;
-    Fc.mt = mt_chunk;
-    Fc.obs_traj = F.obs_traj ? F.obs_traj + i0 * N * S : nullptr;
-    Fc.act_traj = F.act_traj ? F.act_traj + i0 * N * D : nullptr;
-    Fc.rew_traj = F.rew_traj ? F.rew_traj + i0 * N : nullptr;
-    Fc.qty_traj = F.qty_traj ? F.qty_traj + i0 * N * D : nullptr;
+  return launch_spans(C, E, F, eps_chunk, mt_chunk, stream, [&](const FusedArgs& Fc) {
     hipLaunchKernelGGL(fused_resident_kernel, dim3(grid), dim3(kRT), RLds::total, stream, C, st, E, Fc);
-    err = hipGetLastError();
-    if (err != hipSuccess) return err;
-  }
-  return hipSuccess;
+    return hipGetLastError();
+  });
 }
 
 }  // namespace fm

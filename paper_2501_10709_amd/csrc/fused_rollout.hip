@@ -515,7 +515,7 @@ void market_table_kernel(EnvConst C, EnsDev E, int t0, int n_days, float* __rest
   }
 }
 
-// Day blockIdx.y of the chunk, block i of its N * G noise blocks per thread.  Bound by the
+// Day blockIdx.y of the launch, block i of its N * G noise blocks per thread.  Bound by the
 // generator's multiplications.
 __global__ __launch_bounds__(256) void noise_chunk_kernel(uint64_t key, int64_t env_offset, int t0, int N, int D,
                                                           float* __restrict__ eps) {
@@ -1451,52 +1451,26 @@ hipError_t launch_streamed_kernel(const EnvConst& C, const EnvState& st, const E
             E, F);
 }
 
-// The streamed or the wide resident schedule over a rollout: per chunk of at most kFusedChunk
-// steps, the chunk's market table and noise, then the fused kernel for the chunk's steps.
-hipError_t launch_streamed(const EnvConst& C, const EnvState& st, const EnsDev& E, FusedArgs F, int rowt, bool wide,
-                           float* eps_chunk, float* mt_chunk, hipStream_t stream) {
-  const int t_end = F.t0 + F.n_steps;
-  const size_t N = C.N, D = C.D, S = C.S;
-  for (int t = F.t0; t < t_end; t += kFusedChunk) {
-    const int n = t_end - t < kFusedChunk ? t_end - t : kFusedChunk;
-    const size_t i0 = static_cast<size_t>(t - F.t0);
-    hipError_t err = launch_chunk_inputs(C, E, t, n, F.sigma, F.key, F.env_offset, eps_chunk, mt_chunk, stream);
-    if (err != hipSuccess) return err;
-    FusedArgs Fc = F;
-    Fc.t0 = t;
-    Fc.n_steps = n;
-    Fc.eps = eps_chunk;
-    Fc.mt = mt_chunk;
-    Fc.obs_traj = F.obs_traj ? F.obs_traj + i0 * N * S : nullptr;
-    Fc.act_traj = F.act_traj ? F.act_traj + i0 * N * D : nullptr;
-    Fc.rew_traj = F.rew_traj ? F.rew_traj + i0 * N : nullptr;
-    Fc.qty_traj = F.qty_traj ? F.qty_traj + i0 * N * D : nullptr;
-    const int kke = E.ke_pad / 32;
-    if (wide)
-      err = launch_wide_chunk(C, st, E, Fc, stream);
-    else if (rowt == 2)
-      err = kke == 1 ? launch_streamed_kernel<2, 1>(C, st, E, Fc, stream) : launch_streamed_kernel<2, 2>(C, st, E, Fc, stream);
-    else
-      err = kke == 1 ? launch_streamed_kernel<1, 1>(C, st, E, Fc, stream) : launch_streamed_kernel<1, 2>(C, st, E, Fc, stream);
-    if (err != hipSuccess) return err;
-  }
-  return hipSuccess;
+// The streamed or the wide resident schedule over a rollout.
+hipError_t launch_streamed(const EnvConst& C, const EnvState& st, const EnsDev& E, const FusedArgs& F, int rowt,
+                           bool wide, float* eps_chunk, float* mt_chunk, hipStream_t stream) {
+  const int kke = E.ke_pad / 32;
+  return launch_spans(C, E, F, eps_chunk, mt_chunk, stream, [&](const FusedArgs& Fc) {
+    if (wide) return launch_wide_chunk(C, st, E, Fc, stream);
+    if (rowt == 2)
+      return kke == 1 ? launch_streamed_kernel<2, 1>(C, st, E, Fc, stream) : launch_streamed_kernel<2, 2>(C, st, E, Fc, stream);
+    return kke == 1 ? launch_streamed_kernel<1, 1>(C, st, E, Fc, stream) : launch_streamed_kernel<1, 2>(C, st, E, Fc, stream);
+  });
 }
-
 
 }  // namespace
 
 
-hipError_t launch_chunk_inputs(const EnvConst& C, const EnsDev& E, int t, int n, float sigma, uint64_t key,
-                               int64_t env_offset, float* eps_chunk, float* mt_chunk, hipStream_t stream) {
-  const int Fm = (1 + C.I) * C.D;
-  hipLaunchKernelGGL(market_table_kernel, dim3((n + kMtDays - 1) / kMtDays, E.K), dim3(kStreamH),
-                     sizeof(float) * kMtDays * mt_row(Fm), stream, C, E, t, n, mt_chunk);
-  hipError_t err = hipGetLastError();
-  if (err != hipSuccess || sigma == 0.0f) return err;
+hipError_t launch_noise(const EnvConst& C, int t, int n, uint64_t key, int64_t env_offset, float* eps,
+                        hipStream_t stream) {
   const size_t per_day = static_cast<size_t>(C.N) * ((C.D + 3) / 4);
   hipLaunchKernelGGL(noise_chunk_kernel, dim3(static_cast<unsigned>((per_day + 255) / 256), n), dim3(256), 0, stream, key,
-                     env_offset, t, C.N, C.D, eps_chunk);
+                     env_offset, t, C.N, C.D, eps);
   return hipGetLastError();
 }
 
