@@ -517,7 +517,7 @@ __global__ __launch_bounds__(kWaves * 64) void env_row_kernel(EnvConst C, EnvSta
     cash = row_sum(cash, pro[0]);
     cash = row_sum(cash, pro[1]);
     int kown[2] = {0, 0};
-    buy_all_seg(cash, kown, lane, B, C.one_p);
+    buy_all_rows(cash, kown, lane, B, C.one_p);
     double val[2];
 #pragma unroll
     for (int s = 0; s < 2; ++s) {

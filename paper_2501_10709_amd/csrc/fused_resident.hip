@@ -511,7 +511,7 @@ void fused_resident_kernel(EnvConst C, EnvState st, EnsDev E, FusedArgs F) {
       cash = row_sum(cash, pro[0]);
       cash = row_sum(cash, pro[1]);
       int kown[2] = {0, 0};
-      buy_all_seg(cash, kown, lane, B, C.one_p);
+      buy_all_rows(cash, kown, lane, B, C.one_p);
       // Holdings, executed quantities, the new day's position values, value and reward
       // (Section 3.1 reward, reading 8).
       double val[2];

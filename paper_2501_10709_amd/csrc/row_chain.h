@@ -82,101 +82,8 @@ __device__ __forceinline__ double row_sub_impl(double acc, double v, std::intege
 __device__ __forceinline__ double row_shr1(double keep, double v) {
   return __builtin_amdgcn_update_dpp(keep, v, 0x111, 0xf, 0xf, false);
 }
-__device__ __forceinline__ double row_prefix(double start, double x, double& total) {
-#pragma clang fp contract(off)
-  double t = start;
-#pragma unroll
-  for (int r = 0; r < 15; ++r) t = row_shr1(t, t - x);
-  total = row_bcast<15>(t - x);
-  return t;
-}
-
-// The buys of the wavefront's two environments (Section 3.1, readings 5-7), by segments.
-// If every row's cash covers the sum of its whole orders with a margin far above the rounding of
-// 32 subtractions, every whole order fits in sequence: the debits are subtracted in stock order
-// and every order fills.  Otherwise, with cash C at the start of a segment, the candidates are
-// the stocks from dn on with a buy order whose one-share debit fits C (the others cannot buy: the
-// cash only falls during the buys).  Every candidate is assumed to fill its whole order; the row
-// prefix of their debits gives the cash each one meets, exactly as the serial recurrence would,
-// up to the first candidate e whose whole order does not fit that cash.  The candidates before e
-// fill whole; e buys what its cash allows (a partial fill, or nothing when one share does not
-// fit); the next segment starts after e.  A segment therefore covers a run of whole fills at the
-// cost of one prefix.
-__device__ __forceinline__ void buy_all_seg(double& cash, int (&kown)[2], int lane, const BuySet (&B)[2],
-                                            double one_p) {
-#pragma clang fp contract(off)
-  const int jl = lane & 15, rl = (lane >> 4) & 1, rbase = lane & 48;
-  const double total = row_sum(0.0, B[0].deb + B[1].deb);  // any order: only a bound
-  if (__builtin_amdgcn_ballot_w64(!(cash >= total * (1.0 + 0x1p-40))) == 0) {
-    cash = row_sub_impl(cash, B[0].deb, std::make_integer_sequence<int, 16>());
-    cash = row_sub_impl(cash, B[1].deb, std::make_integer_sequence<int, 16>());
-    kown[0] = pq_order(B[0].pq);
-    kown[1] = pq_order(B[1].pq);
-    return;
-  }
-  const int q0 = pq_order(B[0].pq), q1 = pq_order(B[1].pq);
-  const int rsh = lane & 48;  // this lane's row's bits in a ballot
-  int dn = 0;  // the row's next stock to consider
-  for (int it = 0; it <= 32; ++it) {
-    const bool c0 = q0 > 0 && B[0].c1 <= cash && jl >= dn;
-    const bool c1 = q1 > 0 && B[1].c1 <= cash && jl + 16 >= dn;
-    const unsigned long long b0 = __builtin_amdgcn_ballot_w64(c0);
-    if ((b0 | __builtin_amdgcn_ballot_w64(c1)) == 0) break;
-    // A prefix is formed only where some row needs it: stocks 0-15 when a row has candidates
-    // there; stocks 16-31 when a row without a failure among stocks 0-15 has candidates there.
-    double mid = cash, end, p0 = cash, p1;
-    if (b0 != 0) p0 = row_prefix(cash, c0 ? B[0].deb : 0.0, mid);
-    const unsigned long long f0 = __builtin_amdgcn_ballot_w64(c0 && !(B[0].deb <= p0));
-    const bool own_f0 = ((f0 >> rsh) & 0xffffu) != 0;
-    unsigned long long f1 = 0;
-    end = mid;
-    p1 = mid;
-    if (__builtin_amdgcn_ballot_w64(c1 && !own_f0) != 0) {
-      p1 = row_prefix(mid, c1 ? B[1].deb : 0.0, end);
-      f1 = __builtin_amdgcn_ballot_w64(c1 && !(B[1].deb <= p1));
-    }
-    const unsigned m0 = static_cast<unsigned>(f0 & 0xffffu) | (static_cast<unsigned>(f1 & 0xffffu) << 16);
-    const unsigned m1 = static_cast<unsigned>((f0 >> 16) & 0xffffu) | (static_cast<unsigned>((f1 >> 16) & 0xffffu) << 16);
-    const unsigned mine = rl == 0 ? m0 : m1;
-    const int e = mine != 0 ? __builtin_ctz(mine) : 32;  // the row's first failure (32: none)
-    if (c0 && jl < e) kown[0] = q0;
-    if (c1 && jl + 16 < e) kown[1] = q1;
-    if ((f0 | f1) == 0) {  // every row filled all its candidates whole
-      cash = end;
-      break;
-    }
-    const bool hi = e >= 16;
-    const bool owner = e < 32 && (e & 15) == jl;
-    double nc = end;  // a row without a failure: all its candidates filled
-    if (owner) {
-      const double pe = hi ? p1 : p0, c1e = hi ? B[1].c1 : B[0].c1;
-      const long pq = hi ? B[1].pq : B[0].pq;
-      int k = 0;
-      double debit = 0.0;
-      if (c1e <= pe) {
-        bool ok = true;
-        k = partial_fill_sel(pe, static_cast<double>(pq_price(pq)), c1e, pq_order(pq), one_p, debit, ok);
-        if (!ok) {
-          double rc1 = __builtin_amdgcn_rcp(c1e);
-          rc1 = fma(fma(-c1e, rc1, 1.0), rc1, rc1);
-          k = partial_fill(pe, static_cast<double>(pq_price(pq)), rc1, pq_order(pq), one_p, debit);
-        }
-      }
-      kown[hi ? 1 : 0] = k;
-      nc = pe - debit;
-    }
-    const int src = e < 32 ? rbase + (e & 15) : lane;
-    const long nbits = __builtin_bit_cast(long, nc);
-    const int lo = __builtin_amdgcn_ds_bpermute(4 * src, static_cast<int>(nbits));
-    const int hb = __builtin_amdgcn_ds_bpermute(4 * src, static_cast<int>(nbits >> 32));
-    cash = __builtin_bit_cast(
-        double, static_cast<long>((static_cast<unsigned long>(static_cast<unsigned>(hb)) << 32) | static_cast<unsigned>(lo)));
-    dn = e < 32 ? e + 1 : 32;
-  }
-}
-
-// row_sum, and row_prefix, of NQ independent sets step by step, so that their dependent chains fill
-// each other's latencies.
+// row_sum of NQ independent sets step by step, so that their dependent chains fill each other's
+// latencies, and the row prefixes above (t; totals P(16)) likewise.
 template <int NQ, int L = 0>
 __device__ __forceinline__ void row_sums(double (&acc)[NQ], const double (&v)[NQ]) {
 #pragma clang fp contract(off)
@@ -202,12 +109,20 @@ __device__ __forceinline__ void row_prefixes(const double (&start)[NQ], const do
   for (int n = 0; n < NQ; ++n) total[n] = row_bcast<15>(t[n] - x[n]);
 }
 
-// The same for NQ sets of four environments, one per 16-lane row (all four rows differ), the sets
+// The buys (Section 3.1, readings 5-7) of NQ sets of four environments, one per 16-lane row, the sets
 // side by side (the steps below are chains of dependent instructions that leave most issue slots
-// empty).  The first failure of a row usually leaves less cash than one share of its stock, and few
-// later stocks are cheaper, so after one segment the buys go on as events: each row's next stock
-// with a buy order whose one-share debit fits the cash buys its whole order or what the cash
-// allows.  Both forms are exact; an event costs about a third of a segment.
+// empty).  Rows may repeat one another.
+// If every row's cash covers the sum of its whole orders with a margin far above the rounding of
+// 32 subtractions, every whole order fits in sequence: the debits are subtracted in stock order
+// and every order fills.  Otherwise one segment: with cash C, the candidates are the stocks with a
+// buy order whose one-share debit fits C (the others cannot buy: the cash only falls during the
+// buys).  Every candidate is assumed to fill its whole order; the row prefix of their debits gives
+// the cash each one meets, exactly as the serial recurrence would, up to the first candidate e whose
+// whole order does not fit that cash.  The candidates before e fill whole; e buys what its cash
+// allows (a partial fill, or nothing when one share does not fit).  That usually leaves less cash
+// than one share of e, and few later stocks are cheaper, so the buys go on as events: each row's
+// next stock with a buy order whose one-share debit fits the cash buys its whole order or what the
+// cash allows.  Both forms are exact; an event costs about a third of a segment.
 template <int NQ>
 __device__ __forceinline__ void buy_all_seg4(double (&cash)[NQ], int (&kown)[NQ][2], int lane, const BuySet (&B)[NQ][2],
                                              double one_p) {
@@ -332,6 +247,17 @@ __device__ __forceinline__ void buy_all_seg4(double (&cash)[NQ], int (&kown)[NQ]
     if (__builtin_amdgcn_ballot_w64(more) == 0) break;
     fill(e, cash, cash);
   }
+}
+
+// One set.
+__device__ __forceinline__ void buy_all_rows(double& cash, int (&kown)[2], int lane, const BuySet (&B)[2], double one_p) {
+  double c[1] = {cash};
+  int k[1][2] = {{kown[0], kown[1]}};
+  const BuySet S[1][2] = {{B[0], B[1]}};
+  buy_all_seg4<1>(c, k, lane, S, one_p);
+  cash = c[0];
+  kown[0] = k[0][0];
+  kown[1] = k[0][1];
 }
 
 }  // namespace fm
