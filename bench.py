@@ -51,13 +51,15 @@ def env_bytes_per_env_step(D, S):
     return 4 * D + 4 * S + 8 + 4 * D
 
 
-CHUNK = 64  # steps per fused-kernel launch (the library's chunk)
+# Steps per fused launch of a rollout that stores its actions: the days that the market table's scratch
+# (64 days of 8 actors of 512 units) holds of 3 actors of 256.
+SPAN = 64 * 8 * 512 // (3 * 256)
 
 
 # Sources the stock-environment and fused-rollout kernels (and their launch choices) are built from.
 PROFILED_SOURCES = ("api.hip", "crypto_serve.hip", "device_common.h", "ensemble_kernels.hip", "env_kernels.hip",
                     "env_lane.hip",
-                    "fused_resident.hip",
+                    "fused_resident.hip", "fused_wide.hip", "resident_device.h",
                     "fused.h", "fused_rollout.hip", "launch.h", "mlp_device.h", "row_chain.h", "status.h")
 
 
@@ -118,15 +120,15 @@ def time_rollouts(env, n_steps, reps, warmup, stream, **kw):
 
 
 def time_launches(env, n_steps, reps, stream, **kw):
-    """Per-launch durations of a rollout issued chunk by chunk (one fused launch per call).
+    """Per-launch durations of a rollout issued span by span (one fused launch per call).
     Returns a list of (steps, ms) over reps rollouts."""
     import torch
     out, res = None, []
     for _ in range(reps):
         env.reset(return_obs=False)
         evs = []
-        for c0 in range(0, n_steps, CHUNK):
-            n = min(CHUNK, n_steps - c0)
+        for c0 in range(0, n_steps, SPAN):
+            n = min(SPAN, n_steps - c0)
             a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
             a.record(stream)
             out = env.rollout(n, out=None, **kw)
@@ -138,8 +140,8 @@ def time_launches(env, n_steps, reps, stream, **kw):
 
 
 def bench_precision(dev, w, args):
-    """The precision form: N=8192, D=30, T=252, bfloat16 fused path (streamed schedule, the
-    default at this size; the resident schedule timed beside it), states, actions and rewards
+    """The precision form: N=8192, D=30, T=252, bfloat16 fused path (wide resident
+    schedule, the default at this size; the streamed and resident ones timed beside it), states, actions and rewards
     stored.  The action and episode-return errors against the oracle are measured by the GPU
     test suite, not here."""
     import torch
@@ -154,8 +156,8 @@ def bench_precision(dev, w, args):
     kw = dict(ens=ens, sigma=w.sigma, noise_key=w.noise_key, path="fused", store=("obs", "act", "rew"))
     reps = max(5, args.steps // 3)
     out = {"workload": w.name, "dtype": "bf16",
-           "schedule": "streamed (the default past one resident workgroup per compute unit)"}
-    for name, schedule in (("streamed", 1), ("resident", 3)):
+           "schedule": "wide (the default past eight environments per compute unit)"}
+    for name, schedule in (("wide", 0), ("streamed", 1), ("resident", 3)):
         env.set_fused_tuning(schedule=schedule)
         tot, _, _, _ = time_rollouts(env, T, reps, 2, stream, **kw)
         out[name] = {"value": N * T / (float(np.median(tot)) / 1e3), "unit": "env-steps/s",
@@ -166,13 +168,13 @@ def bench_precision(dev, w, args):
     steps = sum(n for n, _ in launches)
     ms = sum(t for _, t in launches)
     tf = flop * N * steps / (ms / 1e3) / 1e12
-    out["value"] = out["streamed"]["value"]
+    out["value"] = out["wide"]["value"]
     out["unit"] = "env-steps/s"
     out["roofline"] = {"bound": "mfma", "achieved": tf, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
-                       "frac": tf / PEAK_BF16_TFLOPS, "kernel": "fused_streamed_kernel",
+                       "frac": tf / PEAK_BF16_TFLOPS, "kernel": "fused_wide_kernel",
                        "launch_ms": ms / len(launches), "steps_per_launch": steps / len(launches),
-                       "launch_includes": "the chunk's market_table_kernel and noise_chunk_kernel",
-                       "traffic": traffic_for("fused_streamed_kernel@8192", N * steps / len(launches))}
+                       "launch_includes": "the launch's market_table_kernel and noise_chunk_kernel",
+                       "traffic": traffic_for("fused_wide_kernel@8192", N * steps / len(launches))}
     del env, ens
     torch.cuda.empty_cache()
     return out
@@ -335,8 +337,10 @@ def bench_learner(dev, w, reps=5):
     torch.cuda.empty_cache()
     return {"workload": f"policy gradient (eqs. 4-5, lambda 0.1) for one of {K} actors {S}-{H}-{H}-{D} from a "
                         f"{N} x {T} rollout", "ms": ms, "samples_per_s": rows / (ms / 1e3),
-            "roofline": {"bound": "fp32", "achieved": tf, "peak": 157.3, "unit": "TFLOP/s", "frac": tf / 157.3,
-                         "kernel": "gemm_kernel (float32 MFMA 16x16x4 tiles)", "flop_per_sample": flop / rows}}
+            "roofline": {"bound": "mfma", "achieved": tf, "peak": PEAK_BF16_TFLOPS / 6, "unit": "TFLOP/s",
+                         "frac": tf / (PEAK_BF16_TFLOPS / 6), "flop_per_sample": flop / rows,
+                         "kernel": "gemm_kernel (a float32 product as six bfloat16 products; the float32 "
+                                   "matrix rate is 157.3)"}}
 
 
 def cpu_baseline(w, budget_s=10.0, max_reps=4):
@@ -578,7 +582,7 @@ def main():
                      "frac": achieved_tf / PEAK_BF16_TFLOPS,
                      "traffic": traffic_for("fused_resident_kernel", N * steps_per_launch),
                      "kernel": "fused_resident_kernel", "launch_ms": mean_launch_ms,
-                     "launch_includes": "the chunk's market_table_kernel and noise_chunk_kernel",
+                     "launch_includes": "the launch's market_table_kernel and noise_chunk_kernel",
                      "steps_per_launch": steps_per_launch, "flop_per_env_step": flop_env_step},
         "env_roofline": {"bound": "hbm", "achieved": achieved_gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                          "frac": achieved_gbs / PEAK_HBM_GBS,

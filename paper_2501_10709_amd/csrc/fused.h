@@ -12,14 +12,14 @@
 
 namespace fm {
 
-// Steps per launch of the streamed schedule; its per-chunk scratch holds this many days.
+// Days of noise that the fused rollout's scratch holds, and steps per launch of the batched form.
 constexpr int kFusedChunk = 64;
-// Scratch floats of the streamed schedule for N environments and D stocks: the chunk's noise
+// Scratch floats of the split-layer schedules for N environments and D stocks: the noise
 // [kFusedChunk][N][D] and market table [kFusedChunk][8][512] (any supported K, H).
 inline size_t fused_eps_floats(size_t N, size_t D) { return static_cast<size_t>(kFusedChunk) * N * D; }
 inline size_t fused_table_floats() { return static_cast<size_t>(kFusedChunk) * 8 * 512; }
 
-// Arguments of a fused launch over a chunk of steps.
+// Arguments of a fused launch over a span of steps.
 struct FusedArgs {
   int t0, n_steps;
   float sigma;
@@ -30,7 +30,7 @@ struct FusedArgs {
   double* rew_traj;
   int* qty_traj;
   const float* eps;  // streamed and resident schedules: the launch's noise [n_steps][N][D] (may be act_traj)
-  const float* mt;   // streamed and resident schedules: the chunk's layer-1 market shares [n_steps][K][H]
+  const float* mt;   // streamed and resident schedules: the launch's layer-1 market shares [n_steps][K][H]
   int tile_envs = 0; // streamed and resident schedules: environments per workgroup
 };
 
@@ -41,10 +41,10 @@ constexpr int kResRows = 8;
 struct FusedTuning {
   int row_tiles = 0;  // streamed: 0 chooses from the problem size
   int schedule = 0;   // 0: resident when the shape allows and N fills at most one workgroup per
-                      // compute unit, else streamed when the shape allows; 1: streamed when the
-                      // shape allows; 2: always the generic schedule; 3: resident whenever the
-                      // shape allows
-  int tile_envs = 0;  // resident / streamed: environments per workgroup, 0: fill the compute units
+                      // compute unit, else wide when the shape allows, else streamed when it
+                      // allows that; 1: streamed when the shape allows; 2: always the generic
+                      // schedule; 3: resident whenever the shape allows
+  int tile_envs = 0;  // resident / wide / streamed: environments per workgroup, 0: fill the compute units
 };
 
 // True when the streamed MLP schedule handles this ensemble and environment.
@@ -92,11 +92,11 @@ hipError_t launch_spans(const EnvConst& C, const EnsDev& E, const FusedArgs& F, 
   return hipSuccess;
 }
 
-// The resident schedule over F's steps, chunk by chunk (fused_resident.hip).
+// The resident schedule over F's steps (fused_resident.hip).
 hipError_t launch_resident(const EnvConst& C, const EnvState& st, const EnsDev& E, FusedArgs F, float* eps_chunk,
                            float* mt_chunk, hipStream_t stream);
 
-// One chunk of the wide resident schedule (fused_wide.hip): the resident schedule's shapes, up to 32
+// One launch of the wide resident schedule (fused_wide.hip): the resident schedule's shapes, up to 32
 // environments per workgroup.
 hipError_t launch_wide_chunk(const EnvConst& C, const EnvState& st, const EnsDev& E, const FusedArgs& F,
                              hipStream_t stream);

@@ -7,7 +7,7 @@
 //     fragments of output tiles 4w .. 4w+3 of every actor, two actors' worth in the accumulation
 //     registers (read in place by the MFMAs) and one in the vector registers;
 //   * W1e (the first layer's rows for the cash and holdings entries) and W3 live in LDS; the
-//     first layer's market rows are folded into the day's table (bias included), made per chunk
+//     first layer's market rows are folded into the day's table (bias included), made per launch
 //     by market_table_kernel, because the closes and indicators are the same for every
 //     environment on a day (Section 3.1 state, shared market data of Section 4.2).
 // The layers run transposed (units x environments, weights as the A operand); the 8 environments
@@ -27,7 +27,7 @@
 //         the fills of its own stocks; holdings, position values, the new value and reward, the
 //         next state row, and the trajectory stores of actions, quantities and rewards straight
 //         from registers.
-// The step's noise (drawn per chunk by noise_chunk_kernel) is requested at the top of a step and
+// The step's noise (drawn per launch by noise_chunk_kernel) is requested at the top of a step and
 // used after the MLP.  The inputs travel by buffer loads that write LDS directly: the next step's
 // table row, a third by each of wavefronts 0-2 at the top of a step (waited for after the third
 // barrier; double-buffered), and the market rows two steps ahead by wavefront 3, which has no
@@ -474,7 +474,6 @@ void fused_resident_kernel(EnvConst C, EnvState st, EnsDev E, FusedArgs F) {
       // ---------------------------------------------------------- the trading step
 #pragma clang fp contract(off)
       const float* in = s_in + bi * kRInBuf;
-      const size_t row = static_cast<size_t>(j) * N + n0 + m;
       const bool store_row = env_ok && lane < 32;  // rows 2 and 3 repeat rows 0 and 1
       const size_t row0 = static_cast<size_t>(j) * N + n0;  // the tile's first row of step j
       const int em = m * D;                                 // environment m's first entry in [M][D]

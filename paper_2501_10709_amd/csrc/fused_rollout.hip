@@ -466,7 +466,7 @@ struct Streamed {
 };
 
 // ------------------------------------------------------------------------------------------
-// Per-chunk tables of the streamed kernel, made before it by two small kernels:
+// Tables of a launch of the streamed, wide or resident kernel, made before it by two small kernels:
 //   mt[c][k][j]: actor k's layer-1 pre-activation share of the market entries of state s_t
 //     (t = t0 + c), b1_k[j] + sum_f bf16(x_f) * W1m_k[f][j] in float32 -- the same for every
 //     environment of day t, so it is computed once per day instead of once per environment;
