@@ -975,9 +975,9 @@ __host__ __device__ inline int generic_areas(int MR, const EnvConst& C, const En
 // it waits for is passed as few times as the results allow: a layer of three actors at once, the
 // trading part in one piece by rows, and the noise, market rows and trajectory stores of a
 // neighbouring step beside it on the wavefronts that it leaves idle.  On 1000 environments of 17
-// stocks, 128 units and three actors a step takes 10.4 us, against 21.1 with a layer of one actor
+// stocks, 128 units and three actors a step takes 10.2 us, against 21.1 with a layer of one actor
 // at a time, four wavefronts and the chain by phases; 24 uneven groups up to 4096 environments and
-// 400 days at 256 units 26.0 ms against 42.6.
+// 400 days at 256 units 25.9 ms against 42.7.
 template <int ROWT, int TMAX, bool ROWS>
 __device__ __forceinline__ void generic_tile(const EnvConst& C, const EnvState& st, const EnsDev& E,
                                              const FusedArgs& F, int tile, unsigned char* smem) {
@@ -1579,8 +1579,8 @@ hipError_t launch_fused_rollout(const EnvConst& C, const EnvState& st, const Ens
   }
   if (tune.schedule != 2 && fused_streamed_shape(C, E)) {
     // The wide resident schedule wherever its shapes allow: at every size past one resident
-    // workgroup per compute unit it takes less than the streamed one (4096 environments 7.8 us a step
-    // against 17.1, 8192 13.4 against 21.0, 32768 51.3 against 82.5).  A round of workgroups, one per
+    // workgroup per compute unit it takes less than the streamed one (4096 environments 7.6 us a step
+    // against 17.0, 8192 13.1 against 20.7, 32768 50.8 against 81.8).  A round of workgroups, one per
     // compute unit, takes 12.5 us at 17 to 32 environments each and 7.0 at up to 16, so the tile is
     // the one whose rounds take less.
     const bool wide = tune.schedule == 0 && tune.row_tiles <= 0 && fused_resident_shape(C, E);
