@@ -969,13 +969,13 @@ __host__ __device__ inline int generic_areas(int MR, const EnvConst& C, const En
   return FusedLds::bytes(MR, st0, E.H + 8, C.D, C.I, kPass) <= kBatchedMaxLds ? kPass : 2;
 }
 
-// One tile (16*ROWT environments starting at tile*16*ROWT) through the steps of F, generic
-// schedule: the body of the generic kernel and of the batched persistent kernel.
+// One tile (F.tile_envs <= 16*ROWT environments starting at tile*F.tile_envs; 0: 16*ROWT) through the
+// steps of F, generic schedule: the body of the generic kernel and of the batched persistent kernel.
 // A step is a chain of latencies (weights from L2, barriers, the serial cash recurrence), so what
 // it waits for is passed as few times as the results allow: a layer of three actors at once, the
 // trading part in one piece by rows, and the noise, market rows and trajectory stores of a
 // neighbouring step beside it on the wavefronts that it leaves idle.  On 1000 environments of 17
-// stocks, 128 units and three actors a step takes 10.2 us, against 21.1 with a layer of one actor
+// stocks, 128 units and three actors a step takes 9.7 us, against 21.1 with a layer of one actor
 // at a time, four wavefronts and the chain by phases; 24 uneven groups up to 4096 environments and
 // 400 days at 256 units 25.9 ms against 42.7.
 template <int ROWT, int TMAX, bool ROWS>
@@ -985,8 +985,9 @@ __device__ __forceinline__ void generic_tile(const EnvConst& C, const EnvState& 
   constexpr int kMk = 3;  // market values per thread of the wavefronts past the owners'
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int D = C.D, N = C.N, DS = D + 1;
-  const int n0 = tile * MR;
-  const int M = min(MR, N - n0);
+  const int tile_envs = F.tile_envs > 0 ? F.tile_envs : MR;
+  const int n0 = tile * tile_envs;
+  const int M = min(tile_envs, N - n0);
   // Split first layer when the day's market tables come with the launch (F.mt, [n_steps][K][H],
   // bias included): layer 1 runs on the ke_pad per-environment entries only.
   const bool split = F.mt != nullptr;
@@ -1009,7 +1010,7 @@ __device__ __forceinline__ void generic_tile(const EnvConst& C, const EnvState& 
   // environment (row_m(q): the row's environment of set q), with the state in registers; wider
   // environments take the chain by phases, a lane per environment, holdings in LDS.
   const int jl = lane & 15;
-  const auto row_m = [&](int q) { return 16 * q + 4 * wave + (lane >> 4); };
+  const auto row_m = [&](int q) { return 16 * q + wave + 4 * (lane >> 4); };
   double cash[ROWT], asset[ROWT], cumrew[ROWT];
   int hold[ROWT][2];
 #pragma unroll
@@ -1416,14 +1417,18 @@ hipError_t go(Kern kern, int grid, int threads, size_t lds, hipStream_t stream, 
   return hipGetLastError();
 }
 
-hipError_t launch_generic(const EnvConst& C, const EnvState& st, const EnsDev& E, const FusedArgs& F,
+hipError_t launch_generic(const EnvConst& C, const EnvState& st, const EnsDev& E, FusedArgs F, int cus,
                           hipStream_t stream, std::string* why) {
   const size_t lds = FusedLds::bytes(16, E.S_pad + 8, E.H + 8, C.D, C.I, generic_areas(16, C, E, E.S_pad + 8));
   if (lds > 160 * 1024) {
     *why = "fused rollout: state and hidden sizes exceed the LDS budget";
     return hipSuccess;
   }
-  const int grid = (C.N + 15) / 16;
+  // Environments per workgroup: fewer than a row tile where that leaves compute units idle (the buys of
+  // a wavefront go on until its last environment is done, and there is less to draw and to store: 1000
+  // environments of 17 stocks 1030 -> 983 us at four a workgroup instead of 16).
+  F.tile_envs = cus > 0 ? std::max(1, std::min(16, (C.N + cus - 1) / cus)) : 16;
+  const int grid = (C.N + F.tile_envs - 1) / F.tile_envs;
   if (E.H <= 2 * 16 * kGenericWaves)
     return go(C.D <= 32 ? fused_generic_kernel<1, 2, true> : fused_generic_kernel<1, 2, false>, grid, kGenericThreads,
               lds, stream, C, st, E, F);
@@ -1598,7 +1603,7 @@ hipError_t launch_fused_rollout(const EnvConst& C, const EnvState& st, const Ens
     *why = "fused rollout: at most 128 stocks";
     return hipSuccess;
   }
-  return launch_generic(C, st, E, F, stream, why);
+  return launch_generic(C, st, E, F, cus, stream, why);
 }
 
 }  // namespace fm

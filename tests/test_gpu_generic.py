@@ -11,7 +11,9 @@ pytestmark = pytest.mark.gpu
 
 # D, N, H, K, T
 SHAPES = [(1, 1, 32, 1, 6), (16, 17, 96, 2, 8), (17, 33, 128, 3, 12), (32, 31, 224, 4, 6), (33, 16, 64, 3, 8),
-          (48, 19, 288, 3, 5), (60, 15, 256, 5, 5), (128, 9, 32, 3, 3)]
+          (48, 19, 288, 3, 5), (60, 15, 256, 5, 5), (128, 9, 32, 3, 3),
+          # three environments a workgroup and sixteen, ragged at the end
+          (20, 700, 64, 2, 5), (36, 4099, 32, 1, 3)]
 
 
 def _np(t):
