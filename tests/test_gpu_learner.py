@@ -164,3 +164,94 @@ def test_policy_gradient_with_infinite_and_huge_inputs():
     err = (got - want)[plain].abs().max() / want[plain].abs().max()
     assert err <= 1e-5, err
     assert torch.equal(torch.isfinite(got), torch.isfinite(want))
+
+
+def _direct(S, H, D, N, T, w, states, rew, sigma, key):
+    """One actor's gradient without the library: float64 on the CPU, with the library's noise."""
+    import torch
+    from paper_2501_10709_amd import binding as B
+    o, p = 0, []
+    for shp in ((S, H), (H,), (H, H), (H,), (H, D), (D,)):
+        p.append(w[o:o + int(np.prod(shp))].cpu().double().reshape(shp))
+        o += int(np.prod(shp))
+    x = states.reshape(T * N, S).cpu().double()
+    h1 = torch.tanh(x @ p[0] + p[1])
+    h2 = torch.tanh(h1 @ p[2] + p[3])
+    mu = torch.tanh(h2 @ p[4] + p[5])
+    eps = torch.empty((T, N, D), device="cuda")
+    for t in range(T):
+        B.fm_noise(key, 0, N, t, D, eps[t])
+    g3 = (rew.sum(0) / N).cpu().repeat(T)[:, None] * eps.reshape(T * N, D).cpu().double() / sigma * (1 - mu * mu)
+    g2 = (g3 @ p[4].t()) * (1 - h2 * h2)
+    g1 = (g2 @ p[2].t()) * (1 - h1 * h1)
+    return (x.t() @ g1, g1.sum(0), h1.t() @ g2, g2.sum(0), h2.t() @ g3, g3.sum(0))
+
+
+def _one_actor(S, H, D, N, T, seed):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    w = torch.randn(S * H + H + H * H + H + H * D + D, generator=g, device="cuda") * 0.2
+    states = torch.randn((T, N, S), generator=g, device="cuda")
+    rew = torch.randn((T, N), generator=g, device="cuda", dtype=torch.float64)
+    return w, states, rew
+
+
+def _gradient(S, H, D, N, T, w, states, rew, sigma, key):
+    import torch
+    from paper_2501_10709_amd import binding as B
+    ws = torch.empty(B.fm_pg_workspace_bytes(1, S, H, D, N, T), dtype=torch.uint8, device="cuda")
+    got = torch.empty(S * H + H + H * H + H + H * D + D, device="cuda")
+    call = lambda: B.fm_policy_gradient(1, S, H, D, w, 0, states, rew, N, T, sigma, key, 0, 0.0, got, ws)  # noqa: E731
+    call()
+    return got, call
+
+
+@pytest.mark.parametrize("S,H,D,N,T", [(9, 32, 3, 41, 3), (36, 64, 33, 9, 7), (33, 96, 5, 700, 3), (20, 128, 40, 77, 4),
+                                       (50, 300, 31, 50, 5), (128, 256, 66, 65, 2)])
+def test_policy_gradient_past_the_bfloat16_range(S, H, D, N, T):
+    """Operands that have no bfloat16 value (an infinite state entry; weights of 3.4e38 in layers 2 and
+    3, whose units saturate) on every layout and tile width of the products, with remainders in rows,
+    columns and terms: all entries that are finite are the gradient's."""
+    import torch
+    w, states, rew = _one_actor(S, H, D, N, T, 11)
+    states[1, 7, 2] = float("inf")
+    w[S * H + H + 3 * H + 5] = 3.4e38
+    w[S * H + H + H * H + H + 4 * D + 1] = -3.4e38
+    got, _ = _gradient(S, H, D, N, T, w, states, rew, 0.1, 1)
+    got = _unflatten(got.cpu().double(), S, H, D)
+    for name, want in zip(NAMES, _direct(S, H, D, N, T, w, states, rew, 0.1, 1)):
+        if name == "W1":
+            keep = torch.arange(S) != 2
+            got[name], want = got[name][keep], want[keep]
+        assert torch.isfinite(want).all() and torch.isfinite(got[name]).all(), name
+        err = (got[name] - want).abs().max() / want.abs().max()
+        assert err <= 1e-5, (name, err)
+
+
+def test_policy_gradient_time_with_a_nan_reward():
+    """One NaN reward makes every entry of the gradient NaN.  It costs a second pass of the products
+    in float32 (about twice the time), and not one element at a time (over a hundred times)."""
+    import torch
+    S, H, D, N, T = 211, 256, 30, 1000, 20
+    w, states, rew = _one_actor(S, H, D, N, T, 5)
+
+    def ms(call):
+        times = []
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            call()
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        return sorted(times)[2]
+
+    got, call = _gradient(S, H, D, N, T, w, states, rew, 0.1, 1)
+    assert torch.isfinite(got).all()
+    plain = ms(call)
+    rew[3, 500] = float("nan")
+    got, call = _gradient(S, H, D, N, T, w, states, rew, 0.1, 1)
+    assert torch.isnan(got).all()
+    nan = ms(call)
+    print(f"  finite {plain:.3f} ms, one NaN reward {nan:.3f} ms", flush=True)
+    assert nan <= 10 * plain, (nan, plain)
