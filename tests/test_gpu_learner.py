@@ -255,3 +255,24 @@ def test_policy_gradient_time_with_a_nan_reward():
     nan = ms(call)
     print(f"  finite {plain:.3f} ms, one NaN reward {nan:.3f} ms", flush=True)
     assert nan <= 10 * plain, (nan, plain)
+
+
+@pytest.mark.parametrize("reward,column,weight", [(1e-36, 1.0, 1.0), (1.0, 1e-36, 1.0), (1.0, 1e-34, 1e34), (1e25, 1.0, 1.0),
+                                                  (1e30, 1.0, 1.0)])
+def test_policy_gradient_at_the_ends_of_the_float32_range(reward, column, weight):
+    """Rewards, and one state column with its weights, at magnitudes where a part of a split operand
+    leaves the bfloat16 range or a scaled sum the float32 one; each row of a matrix is held to its own
+    largest entry.  (Rewards of 1e-37 make subnormal deltas, of fewer bits in float32 itself.)"""
+    import torch
+    S, H, D, N, T = 40, 96, 7, 200, 12
+    w, states, rew = _one_actor(S, H, D, N, T, 21)
+    rew *= reward
+    states[:, :, 3] *= column
+    w[3 * H:4 * H] *= weight
+    got, _ = _gradient(S, H, D, N, T, w, states, rew, 0.1, 1)
+    got = _unflatten(got.cpu().double(), S, H, D)
+    for name, want in zip(NAMES, _direct(S, H, D, N, T, w, states, rew, 0.1, 1)):
+        scale = want.abs().amax(-1, keepdim=True)
+        err = ((got[name] - want).abs() / scale).max()
+        print(f"  {name}: largest {scale.max():.1e}, error {err:.1e}", flush=True)
+        assert err <= 1e-5, (name, err)
