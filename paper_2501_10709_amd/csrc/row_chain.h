@@ -123,7 +123,10 @@ __device__ __forceinline__ void row_prefixes(const double (&start)[NQ], const do
 // than one share of e, and few later stocks are cheaper, so the buys go on as events: each row's
 // next stock with a buy order whose one-share debit fits the cash buys its whole order or what the
 // cash allows.  Both forms are exact; an event costs about a third of a segment.
-template <int NQ>
+// LEAVE: wavefronts without a candidate leave before the segment (agents that only buy are soon there:
+// 100 given days of 30 stocks and 2048 environments take 188 us against 221, of 32 and 8192 375 against 418).  The
+// generic schedules go without: the branch costs their batched form's registers up to 4%.
+template <int NQ, bool LEAVE = true>
 __device__ __forceinline__ void buy_all_seg4(double (&cash)[NQ], int (&kown)[NQ][2], int lane, const BuySet (&B)[NQ][2],
                                              double one_p) {
 #pragma clang fp contract(off)
@@ -147,6 +150,14 @@ __device__ __forceinline__ void buy_all_seg4(double (&cash)[NQ], int (&kown)[NQ]
       kown[n][1] = pq_order(B[n][1].pq);
     }
     return;
+  }
+  if constexpr (LEAVE) {
+    bool some = false;
+#pragma unroll
+    for (int n = 0; n < NQ; ++n)
+#pragma unroll
+      for (int s = 0; s < 2; ++s) some = some || (pq_order(B[n][s].pq) > 0 && B[n][s].c1 <= cash[n]);
+    if (__builtin_amdgcn_ballot_w64(some) == 0) return;
   }
   // One segment: every candidate's cash if those before it fill whole.
   double at[2][NQ], mid[NQ], end[NQ];  // the cash that the lane's stocks meet; after 16; after them all

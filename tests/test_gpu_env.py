@@ -278,3 +278,30 @@ def test_rollout_past_horizon_is_a_state_error():
     with pytest.raises(FmError):
         env.rollout(1, actions=acts[:1])
     env.rollout(0, actions=acts[:0])  # zero steps is a no-op
+
+
+@pytest.mark.parametrize("N,D,M,dear", [(6, 10, 1, False), (37, 30, 1, False), (38, 32, 2, False), (21, 17, 2, True)])
+def test_row_kernel_with_cash_used_up(N, D, M, dear):
+    """Agents that only buy: after a day or two no stock of a wavefront can be bought, except where
+    every fifth environment sells and goes on.  `dear`: the first stock alone uses up the cash, and what
+    is left buys the others in part."""
+    import torch
+    from paper_2501_10709_amd.vecenv import VecEnv
+    dev = cuda()
+    T = 9
+    cfg, m = env_case(N, D, 2, T, 17, cash=2e5)
+    close = m.close.copy()
+    if dear:
+        close[:, 0] *= 300
+    acts = np.abs(make_actions(23, T, N, D))
+    acts[4:, ::5, ::2] *= -1
+    env = VecEnv(cfg, close, m.ind, device=dev)
+    env.set_step_kernel(3, M)
+    env.reset(return_obs=False)
+    traj = {k: _to_np(v) for k, v in env.rollout(T, actions=torch.from_numpy(acts).to(dev)).items()}
+    ref = rollout_driven(cfg, close, m.ind, acts)
+    assert np.array_equal(traj["qty"], ref["exec"])
+    assert np.array_equal(traj["obs"], ref["obs"][1:])
+    idle = (ref["exec"] == 0).all(axis=2)
+    assert idle.any() and (ref["exec"] > 0).any(), "the data must reach both sides"
+    assert np.array_equal(_to_np(env.read_state()["cash"]), ref["cash"])
