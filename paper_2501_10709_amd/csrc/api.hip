@@ -347,10 +347,12 @@ hipError_t batch_enqueue(fm_batch* b, int n_chunks, hipStream_t stream) {
     const unsigned char* desc = b->d_desc + b->desc_bytes * b->n_groups * c;
     const int* items = b->d_items + 2 * b->items_cap * c;
     const int nw = b->n_wide[c], nn = b->n_items[c] - nw;
+    int actors = 0;
+    for (const fm_batch_group& G : b->groups) actors = std::max(actors, G.ens->E.K);
     hipError_t e = hipSuccess;
-    if (nw > 0) e = fm::launch_batched(32, b->blocks, b->lds_wide, desc, items, nw, b->d_counter, stream);
+    if (nw > 0) e = fm::launch_batched(32, actors, b->blocks, b->lds_wide, desc, items, nw, b->d_counter, stream);
     if (e == hipSuccess && nn > 0)
-      e = fm::launch_batched(16, b->blocks, b->lds, desc, items + 2 * nw, nn, b->d_counter + 1, stream);
+      e = fm::launch_batched(16, actors, b->blocks, b->lds, desc, items + 2 * nw, nn, b->d_counter + 1, stream);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

@@ -124,8 +124,8 @@ void batched_group_desc(const EnvConst& C, const EnvState& st, const EnsDev& E, 
 // stream capture.
 size_t batched_max_lds();
 hipError_t prepare_batched(size_t lds);
-// items: int2 (group, tile) pairs; counter: one int of device scratch.
-hipError_t launch_batched(int rows, int blocks, size_t lds, const void* groups, const int* items, int n_items,
+// actors: the most that a group has; items: int2 (group, tile) pairs; counter: one int of device scratch.
+hipError_t launch_batched(int rows, int actors, int blocks, size_t lds, const void* groups, const int* items, int n_items,
                           int* counter, hipStream_t stream);
 
 }  // namespace fm

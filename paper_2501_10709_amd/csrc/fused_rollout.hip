@@ -363,12 +363,11 @@ __device__ __forceinline__ void pass_products(const PassLayer& P, int lane, floa
     if (g + s < P.kend) products(s, g + s);
 }
 
-// kp actors (1..kPass) and tj tiles of the wavefront (0..TM).
-template <int ROWT, int TM>
-__device__ __forceinline__ void pass_layer(const PassLayer& P, int kp, int tj, int lane,
-                                           floatx4 (&acc)[kPass][ROWT][TM]) {
+// kp actors (1..KM) and tj tiles of the wavefront (0..TM).
+template <int ROWT, int TM, int KM>
+__device__ __forceinline__ void pass_layer(const PassLayer& P, int kp, int tj, int lane, floatx4 (&acc)[KM][ROWT][TM]) {
 #pragma unroll
-  for (int k = 0; k < kPass; ++k)
+  for (int k = 0; k < KM; ++k)
 #pragma unroll
     for (int r = 0; r < ROWT; ++r)
 #pragma unroll
@@ -376,9 +375,9 @@ __device__ __forceinline__ void pass_layer(const PassLayer& P, int kp, int tj, i
   static_for<TM>([&](auto ji) {
     constexpr int TJ = ji + 1, RING = TJ <= 2 ? 4 : 2;
     if (tj != TJ) return;
-    if (kp == 1) pass_products<ROWT, 1, TJ, RING>(P, lane, acc);
-    else if (kp == 2) pass_products<ROWT, 2, TJ, RING>(P, lane, acc);
-    else pass_products<ROWT, 3, TJ, RING>(P, lane, acc);
+    static_for<KM>([&](auto ki) {
+      if (kp == ki + 1) pass_products<ROWT, ki + 1, TJ, RING>(P, lane, acc);
+    });
   });
 }
 
@@ -978,7 +977,8 @@ __host__ __device__ inline int generic_areas(int MR, const EnvConst& C, const En
 // stocks, 128 units and three actors a step takes 9.7 us, against 21.1 with a layer of one actor
 // at a time, four wavefronts and the chain by phases; 24 uneven groups up to 4096 environments and
 // 400 days at 256 units 25.9 ms against 42.7.
-template <int ROWT, int TMAX, bool ROWS>
+// KM: actors of a pass at most.
+template <int ROWT, int TMAX, bool ROWS, int KM = kPass>
 __device__ __forceinline__ void generic_tile(const EnvConst& C, const EnvState& st, const EnsDev& E,
                                              const FusedArgs& F, int tile, unsigned char* smem) {
   constexpr int NT = kGenericThreads, NW = kGenericWaves, MR = 16 * ROWT;
@@ -993,7 +993,7 @@ __device__ __forceinline__ void generic_tile(const EnvConst& C, const EnvState& 
   const bool split = F.mt != nullptr;
   const int kin1 = split ? E.ke_pad : E.S_pad;
   const int st0 = kin1 + 8, sth = E.H + 8;
-  const int areas = generic_areas(MR, C, E, st0);
+  const int areas = min(KM, generic_areas(MR, C, E, st0));
 
   const int me = wave * (MR / kOwnerWaves) + lane, n = n0 + me;
   const bool owner = wave < kOwnerWaves && lane < MR / kOwnerWaves && me < M;
@@ -1190,7 +1190,7 @@ __device__ __forceinline__ void generic_tile(const EnvConst& C, const EnvState& 
     for (int k0 = 0; k0 < E.K; k0 += areas) {
       const int kp = min(areas, E.K - k0);
       const unsigned char* PA = E.base + static_cast<size_t>(k0) * E.actor_stride;
-      floatx4 acc[kPass][ROWT][TMAX];
+      floatx4 acc[KM][ROWT][TMAX];
 #pragma unroll 1
       for (int l = 0; l < 3; ++l) {
         const bool own3 = l == 2 && sl3 > 1;
@@ -1217,10 +1217,10 @@ __device__ __forceinline__ void generic_tile(const EnvConst& C, const EnvState& 
           Q.kbeg = q3 * kk3 / sl3;
           Q.kend = (q3 + 1) * kk3 / sl3;
         }
-        float bv[kPass][TMAX];
+        float bv[KM][TMAX];
         const int cols = l < 2 ? E.H : E.A;
 #pragma unroll
-        for (int k = 0; k < kPass; ++k)
+        for (int k = 0; k < KM; ++k)
 #pragma unroll
           for (int j = 0; j < TMAX; ++j) {
             // Sliced: wavefront c + at * (row tile) completes tile c.
@@ -1228,11 +1228,11 @@ __device__ __forceinline__ void generic_tile(const EnvConst& C, const EnvState& 
             bv[k][j] = 0.0f;
             if (k < kp && col < cols) bv[k][j] = gbl(reinterpret_cast<const float*>(bias + k * bstride))[col];
           }
-        pass_layer<ROWT>(Q, kp, tj, lane, acc);
+        pass_layer(Q, kp, tj, lane, acc);
         if (l > 0) __syncthreads();  // the hidden rows are written over
         if (l < 2) {
 #pragma unroll
-          for (int k = 0; k < kPass; ++k)
+          for (int k = 0; k < KM; ++k)
 #pragma unroll
             for (int j = 0; j < TMAX; ++j)
               if (k < kp && j < tj)
@@ -1257,7 +1257,7 @@ __device__ __forceinline__ void generic_tile(const EnvConst& C, const EnvState& 
           for (int q = 0; q < 4; ++q)
             sum[q] = k0 > 0 && col < E.A ? L.abar[(r * 16 + row_q + q) * DS + col] : 0.0f;
 #pragma unroll
-          for (int k = 0; k < kPass; ++k)
+          for (int k = 0; k < KM; ++k)
             if (k < kp) {
               const floatx4 v = value(k);
               const float wk = gbl(E.mix)[k0 + k];
@@ -1284,7 +1284,7 @@ __device__ __forceinline__ void generic_tile(const EnvConst& C, const EnvState& 
           floatx4* part = reinterpret_cast<floatx4*>(L.x1);
           if (tj > 0)
 #pragma unroll
-            for (int k = 0; k < kPass; ++k)
+            for (int k = 0; k < KM; ++k)
               if (k < kp)
 #pragma unroll
                 for (int r = 0; r < ROWT; ++r) part[k * area + ((q3 * at + c3) * ROWT + r) * 64 + lane] = acc[k][r][0];
@@ -1371,7 +1371,7 @@ struct GroupDesc {
   FusedArgs F;
 };
 
-template <int ROWT, int TMAX>
+template <int ROWT, int TMAX, int KM>
 __global__ __launch_bounds__(kGenericThreads) void fused_batched_kernel(const GroupDesc* __restrict__ groups,
                                                             const int2* __restrict__ items, int n_items,
                                                             int* __restrict__ counter) {
@@ -1397,9 +1397,9 @@ __global__ __launch_bounds__(kGenericThreads) void fused_batched_kernel(const Gr
     __builtin_memcpy(&G, w, sizeof(GroupDesc));
     if (G.F.n_steps <= 0) continue;
     if (G.C.D <= 32)
-      generic_tile<ROWT, TMAX, true>(G.C, G.st, G.E, G.F, tile, smem);
+      generic_tile<ROWT, TMAX, true, KM>(G.C, G.st, G.E, G.F, tile, smem);
     else
-      generic_tile<ROWT, TMAX, false>(G.C, G.st, G.E, G.F, tile, smem);
+      generic_tile<ROWT, TMAX, false, KM>(G.C, G.st, G.E, G.F, tile, smem);
   }
 }
 
@@ -1514,27 +1514,33 @@ void batched_group_desc(const EnvConst& C, const EnvState& st, const EnsDev& E, 
 }
 
 hipError_t prepare_batched(size_t lds) {
-  for (const void* k : {reinterpret_cast<const void*>(fused_batched_kernel<1, 2>),
-                        reinterpret_cast<const void*>(fused_batched_kernel<2, 2>)}) {
+  for (const void* k : {reinterpret_cast<const void*>(fused_batched_kernel<1, 2, 2>),
+                        reinterpret_cast<const void*>(fused_batched_kernel<2, 2, 2>),
+                        reinterpret_cast<const void*>(fused_batched_kernel<1, 2, kPass>),
+                        reinterpret_cast<const void*>(fused_batched_kernel<2, 2, kPass>)}) {
     const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
 
-hipError_t launch_batched(int rows, int blocks, size_t lds, const void* groups, const int* items, int n_items,
-                          int* counter, hipStream_t stream) {
+hipError_t launch_batched(int rows, int actors, int blocks, size_t lds, const void* groups, const int* items,
+                          int n_items, int* counter, hipStream_t stream) {
   if (lds > kBatchedMaxLds) return hipErrorInvalidValue;
   hipLaunchKernelGGL(zero_counter_kernel, dim3(1), dim3(64), 0, stream, counter);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const GroupDesc* g = static_cast<const GroupDesc*>(groups);
-  const int2* it = reinterpret_cast<const int2*>(items);
-  if (rows == 32)
-    hipLaunchKernelGGL((fused_batched_kernel<2, 2>), dim3(blocks), dim3(kGenericThreads), lds, stream, g, it, n_items, counter);
-  else
-    hipLaunchKernelGGL((fused_batched_kernel<1, 2>), dim3(blocks), dim3(kGenericThreads), lds, stream, g, it, n_items, counter);
-  return hipGetLastError();
+  // Two actors a pass where no group has more: the form of three spills registers (237 of 32-row tiles
+  // against 62).  30 days of 2 x 4000 environments, 5 and 17 stocks and two actors of 64 units take
+  // 383 us against 614, 8000 of 5 stocks and one actor 313 against 537; with three actors the third is a
+  // pass of its own, and 24 uneven groups take 28.1 ms against 25.9.
+  const auto go_batched = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(kGenericThreads), lds, stream, static_cast<const GroupDesc*>(groups),
+                       reinterpret_cast<const int2*>(items), n_items, counter);
+    return hipGetLastError();
+  };
+  if (rows == 32) return actors <= 2 ? go_batched(fused_batched_kernel<2, 2, 2>) : go_batched(fused_batched_kernel<2, 2, kPass>);
+  return actors <= 2 ? go_batched(fused_batched_kernel<1, 2, 2>) : go_batched(fused_batched_kernel<1, 2, kPass>);
 }
 
 hipError_t launch_fused_rollout(const EnvConst& C, const EnvState& st, const EnsDev& E, int t0, int n_steps,

@@ -164,3 +164,37 @@ def test_batch_hidden_256_matches_oracle(tiling):
         for k in e:
             assert torch.equal(o[k], e[k]), (g, k)
     batch.close()
+
+
+@pytest.mark.parametrize("rows", [16, 32])
+def test_batch_by_actor_counts(rows):
+    """Groups of one and two actors by themselves (two actors a pass) and beside groups of three and
+    four (three a pass): against the oracle, and the same bit for bit in both batches."""
+    import torch
+    from paper_2501_10709_amd.vecenv import Batch, Ensemble, VecEnv
+    dev = cuda()
+    made = []
+    for D, N, T, seed, K, width in [(5, 40, 20, 51, 1, 64), (33, 19, 9, 52, 2, 96), (30, 33, 66, 53, 2, 256),
+                                    (17, 21, 12, 54, 3, 128), (7, 35, 10, 55, 4, 32)]:
+        cfg, m = env_case(N, D, 5, T, seed)
+        _, actors, packed = actors_case(K, 7 * D + 1, width, D, seed_base=100 * seed)
+        ens = Ensemble(packed, K, 7 * D + 1, width, D, dtype="bf16", max_batch=N, device=dev)
+        made.append((cfg, m, actors, ens, VecEnv(cfg, m.close, m.ind, device=dev)))
+    runs = []
+    for n in (3, 5):
+        obs0 = [_np(env.reset()) for *_, env in made[:n]]
+        batch = Batch(_spec(made[:n]))
+        batch.set_tiling(rows, 64)
+        print(f"[batch] {n} groups, {rows} rows", flush=True)
+        out = batch.run()
+        torch.cuda.synchronize()
+        runs.append([{k: v.clone() for k, v in o.items()} for o in out])
+        for i, (cfg, m, actors, ens, env) in enumerate(made[:n]):
+            traj = {k: _np(v) for k, v in runs[-1][i].items()}
+            check_replay(cfg, m, traj, obs0[i])
+            check_actions(actors, "bf16", traj, obs0[i], 0.1, 7, TOL_BF16, env_offset=1000 * i)
+            assert np.abs(traj["qty"]).sum() > 0
+        batch.close()
+    for i in range(3):
+        for k in runs[0][i]:
+            assert torch.equal(runs[0][i][k], runs[1][i][k]), (i, k)
