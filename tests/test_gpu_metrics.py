@@ -60,3 +60,21 @@ def test_metrics_at_pass_and_tile_edges(N, T):
     got = B.fm_backtest_metrics(torch.from_numpy(r).to(dev), 1e6, 2.0 ** -12).cpu().numpy()
     want = backtest_metrics(r, 1e6, 2.0 ** -12)
     assert _close(got, want).all(), (got, want)
+
+
+@pytest.mark.parametrize("N,T", [(300, 31), (300, 32), (6144, 32), (6145, 47), (8192, 48), (8193, 48), (8200, 60), (20000, 6),
+                                 (8300, 300)])
+def test_metrics_on_both_sides_of_the_kernel_choice(N, T):
+    """Many environments, several blocks with a ragged last one, short and long curves, a risk-free rate
+    and starting values of each environment's own."""
+    import torch
+    from paper_2501_10709_amd import binding as B
+    dev = cuda()
+    rng = np.random.default_rng(N + T)
+    r = rng.normal(0.1, 2.0, (T, N))
+    v0 = rng.uniform(0.5e6, 2e6, N)
+    got = B.fm_backtest_metrics(torch.from_numpy(r).to(dev), 1e6, 2.0 ** -12, 252.0, 0.02,
+                                d_init_asset=torch.from_numpy(v0).to(dev)).cpu().numpy()
+    want = backtest_metrics(r, v0, 2.0 ** -12, 252.0, 0.02)
+    ok = _close(got, want)
+    assert ok.all(), (np.argwhere(~ok)[:5], got[~ok][:5], want[~ok][:5])
