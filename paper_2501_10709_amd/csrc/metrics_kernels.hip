@@ -234,8 +234,10 @@ hipError_t launch_metrics(const double* rew, int T, int N, double v0, const doub
   // in several rounds while the second kind still has at most a wavefront per SIMD: 252 days of
   // 2048 environments take 26 us against 174, of 8192 61 against 190, of 16384 117 against 196 (but
   // 61 days of them 48 against 32).  Over a few days its fixed work (all of a pass's divisions)
-  // does not pay: one day of 8192 environments takes 18 us against 8.7, launch included.
-  if (N <= 8192 && T >= 32)
+  // does not pay: one day of 8192 environments takes 18 us against 8.7, launch included.  Whole calls: 32
+  // days of 2048 take 27 us against 35, of 6144 35 against 36; 40 days of 8192 40 against 39, 48 of them
+  // 40 against 43.
+  if (N <= 8192 && T >= (N <= 6144 ? 32 : 48))
     hipLaunchKernelGGL(metrics_kernel, dim3((N + kEnvs - 1) / kEnvs), dim3(kThreads), 0, stream, rew, T, N, v0, v0s,
                        reward_scale, periods_per_year, risk_free, out);
   else
