@@ -306,6 +306,8 @@ void fused_wide_kernel(EnvConst C, EnvState st, EnsDev E, FusedArgs F) {
     }
     if (tid < K) s_mix[tid] = E.mix[tid];
     for (int i = tid; i < MR * kRX0; i += kWT) s_x0[i] = static_cast<__bf16>(0.0f);
+    // Rows past M trade too: without cash, which covers their empty orders.
+    if (tid < 4 * MR) reinterpret_cast<double*>(smem + L::state)[tid] = 0.0;
     for (int i = tid; i < kRInBuf; i += kWT) {  // the first step's market rows
       float v = 0.0f;
       if (i < 2 * D) v = C.close[static_cast<size_t>(F.t0) * D + i];
