@@ -118,6 +118,7 @@ struct fm_env {
 
 struct fm_ensemble {
   int K, S, H, A, dtype, max_batch, device;
+  int units;  // compute units of the device (asked for once: it takes 0.4 us)
   fm::EnsDev E;
   float* mu;  // [K][max_batch][A]
 };
@@ -740,7 +741,7 @@ fm_status env_rollout(fm_env* env, const fm_ensemble* ens, int32_t n_steps,
   const float* obs_in = env->obs_stage;
   for (int i = 0; i < n_steps; ++i) {
     const int t = env->day + i;
-    s = device_status(fm::launch_mlp(ens->dtype, ens->E, obs_in, C.N, ens->mu, st), "env_rollout (mlp)");
+    s = device_status(fm::launch_mlp(ens->dtype, ens->E, ens->units, obs_in, C.N, ens->mu, st), "env_rollout (mlp)");
     if (s != FM_OK) return s;
     float* obs_out = opts->d_obs_traj ? opts->d_obs_traj + static_cast<size_t>(i) * N * S : env->obs_stage;
     float* act_out = opts->d_act_traj ? opts->d_act_traj + static_cast<size_t>(i) * N * D : nullptr;
@@ -857,6 +858,10 @@ fm_status ensemble_create(int32_t K, int32_t S, int32_t H, int32_t A, int32_t dt
   e->dtype = dtype;
   e->max_batch = max_batch;
   if (hipGetDevice(&e->device) != hipSuccess) e->device = 0;
+  if (hipDeviceGetAttribute(&e->units, hipDeviceAttributeMultiprocessorCount, e->device) != hipSuccess) {
+    (void)hipGetLastError();
+    e->units = 256;
+  }
   unsigned char* base = static_cast<unsigned char*>(d_workspace);
   fm::EnsDev& E = e->E;
   E.K = K;
@@ -929,7 +934,8 @@ fm_status ensemble_act(const fm_ensemble* ens, const float* d_obs, int32_t n, fl
   if (env_offset < 0) return fail(FM_ERR_INVALID, "env_offset must be >= 0");
   if (n == 0) return FM_OK;
   DeviceGuard g(ens->device);
-  fm_status s = device_status(fm::launch_mlp(ens->dtype, ens->E, d_obs, n, ens->mu, stream), "ensemble_act (mlp)");
+  fm_status s = device_status(fm::launch_mlp(ens->dtype, ens->E, ens->units, d_obs, n, ens->mu, stream),
+                              "ensemble_act (mlp)");
   if (s != FM_OK) return s;
   return device_status(fm::launch_combine(ens->K, n, ens->A, ens->mu, ens->E.mix, sigma, noise_key, t, env_offset,
                                           d_mean, d_act, stream),

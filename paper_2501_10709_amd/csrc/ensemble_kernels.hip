@@ -81,8 +81,6 @@ __global__ void copy_pad_kernel(const float* __restrict__ src, int n, int n_pad,
   if (i < n_pad) dst[i] = i < n ? src[i] : 0.0f;
 }
 
-// Compute units of the card.
-constexpr int kUnits = 256;
 // Wavefronts of an MLP workgroup; a wavefront owns output tiles wave and wave + 16 of every layer.
 constexpr int kMlpWaves = 16;
 
@@ -349,7 +347,7 @@ __global__ void combine_kernel(int K, int n, int A, const float* __restrict__ mu
 }
 
 template <int DT>
-hipError_t launch_mlp_dt(const EnsDev& E, const float* obs, int n, float* mu, hipStream_t stream) {
+hipError_t launch_mlp_dt(const EnsDev& E, int units, const float* obs, int n, float* mu, hipStream_t stream) {
   // Sixteen wavefronts on tiles of 32 rows (each weight fragment serves two row tiles), or of 16
   // where those leave compute units idle.  Batches of at most 16 rows cut layer 3 into the
   // slices of a four-wavefront workgroup, larger ones into those of sixteen, whatever the tile.
@@ -357,7 +355,7 @@ hipError_t launch_mlp_dt(const EnsDev& E, const float* obs, int n, float* mu, hi
   const auto lds_of = [&](int rt) { return static_cast<size_t>(16 * rt) * (std::max(st0, sth) + sth) * MT<DT>::kElem; };
   const bool fits = lds_of(2) <= 160 * 1024;
   const int tiles = (n + 15) / 16;
-  const int rt = fits && tiles * E.K > kUnits ? 2 : 1;
+  const int rt = fits && tiles * E.K > units ? 2 : 1;
   // A batch past 16 rows is refused where a 32-row tile does not fit the LDS.
   const int s0 = act_stride<DT>(E.S_pad), sh = act_stride<DT>(E.H);
   if (n > 16 && static_cast<size_t>(32) * (std::max(s0, sh) + sh) * MT<DT>::kElem > 160 * 1024)
@@ -414,10 +412,10 @@ hipError_t launch_copy_pad(const float* src, int n, int n_pad, float* dst, hipSt
   return hipGetLastError();
 }
 
-hipError_t launch_mlp(int dtype, const EnsDev& E, const float* obs, int n, float* mu,
+hipError_t launch_mlp(int dtype, const EnsDev& E, int units, const float* obs, int n, float* mu,
                       hipStream_t stream) {
-  return dtype == kF32 ? launch_mlp_dt<kF32>(E, obs, n, mu, stream)
-                       : launch_mlp_dt<kBF16>(E, obs, n, mu, stream);
+  return dtype == kF32 ? launch_mlp_dt<kF32>(E, units, obs, n, mu, stream)
+                       : launch_mlp_dt<kBF16>(E, units, obs, n, mu, stream);
 }
 
 hipError_t launch_combine(int K, int n, int A, const float* mu, const float* mix, float sigma,

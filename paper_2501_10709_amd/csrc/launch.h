@@ -55,7 +55,8 @@ hipError_t launch_copy_pad(const float* src, int n, int n_pad, float* dst, hipSt
 // MFMA fragments over ke_pad rows; the market rows (1..A, 2A+1..S-1) as bfloat16 [S-1-A][H].
 hipError_t launch_pack_env_rows(const float* w1, int A, int H, int ke_pad, void* out, hipStream_t stream);
 hipError_t launch_gather_market_rows(const float* w1, int S, int H, int A, __bf16* out, hipStream_t stream);
-hipError_t launch_mlp(int dtype, const EnsDev& E, const float* obs, int n, float* mu,
+// units: compute units of the device.
+hipError_t launch_mlp(int dtype, const EnsDev& E, int units, const float* obs, int n, float* mu,
                       hipStream_t stream);
 hipError_t launch_combine(int K, int n, int A, const float* mu, const float* mix, float sigma,
                           uint64_t key, int t, int64_t env_offset, float* mean, float* act,
