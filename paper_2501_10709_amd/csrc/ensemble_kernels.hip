@@ -356,10 +356,10 @@ hipError_t launch_mlp_dt(const EnsDev& E, int units, const float* obs, int n, fl
   const bool fits = lds_of(2) <= 160 * 1024;
   const int tiles = (n + 15) / 16;
   const int rt = fits && tiles * E.K > units ? 2 : 1;
-  // A batch past 16 rows is refused where a 32-row tile does not fit the LDS.
-  const int s0 = act_stride<DT>(E.S_pad), sh = act_stride<DT>(E.H);
-  if (n > 16 && static_cast<size_t>(32) * (std::max(s0, sh) + sh) * MT<DT>::kElem > 160 * 1024)
-    return hipErrorInvalidValue;
+  // The library's limit on float32 networks past 16 rows: state width (rounded up to 32) and hidden width
+  // together below 1280, where 32 rows of both with two floats of padding each fill 160 KB.  (Tiles of 16
+  // rows would go further; what a call accepts does not depend on the tile that it takes.)
+  if (DT == kF32 && n > 16 && round_up(E.S_pad, 32) + E.H >= 1280) return hipErrorInvalidValue;
   const int nt3 = E.A_pad / 16, nk3 = E.H / MT<DT>::kKGroup;
   const int cap = 16 * sth * MT<DT>::kElem / (nt3 * 1024);
   const int slices = std::max(1, std::min(std::min((n > 16 ? kMlpWaves : 4) / nt3, nk3), cap));

@@ -41,13 +41,6 @@ struct MT<kBF16> {
 
 __host__ __device__ inline int round_up(int x, int m) { return (x + m - 1) / m * m; }
 
-// Row stride (elements) of an LDS activation tile with kin_pad columns: keeps the MFMA
-// A-operand reads free of bank conflicts.
-template <int DT>
-__host__ __device__ inline int act_stride(int kin_pad) {
-  return DT == kF32 ? round_up(kin_pad, 32) + 2 : kin_pad + 8;
-}
-
 // Device view of a packed ensemble.
 struct EnsDev {
   int K, S, H, A;
