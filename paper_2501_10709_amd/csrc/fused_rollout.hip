@@ -1425,9 +1425,16 @@ hipError_t launch_generic(const EnvConst& C, const EnvState& st, const EnsDev& E
     return hipSuccess;
   }
   // Environments per workgroup: fewer than a row tile where that leaves compute units idle (the buys of
-  // a wavefront go on until its last environment is done, and there is less to draw and to store: 1000
-  // environments of 17 stocks 1030 -> 983 us at four a workgroup instead of 16).
-  F.tile_envs = cus > 0 ? std::max(1, std::min(16, (C.N + cus - 1) / cus)) : 16;
+  // a wavefront go on until its last environment is done, and there is less to draw and to store), which
+  // gains with the stocks; but every workgroup streams all weights every step, which costs with their
+  // bytes.  Against sixteen a workgroup, over 64 to 512 units, 1 to 8 actors, 5 to 100 stocks, 100 to 4000
+  // environments and rollouts of 16 and 100 days: up to 24 KB of weights a stock 0.81 to 1.03 of the time (1000
+  // environments of 17 stocks and 216 KB, 100 days, 973 us against 978; of 50 and 408 KB 0.91); past that
+  // up to 1.11 (30 stocks, 2.3 MB, 1000 environments, 16 days: 555 us against 498), except at one or two
+  // environments a workgroup (0.88 to 1.03); past twelve a workgroup 0.99 to 1.04 throughout.
+  const size_t weights = 2 * static_cast<size_t>(E.K) * E.H * (E.S_pad + E.H + E.A_pad);
+  const int per_unit = cus > 0 ? (C.N + cus - 1) / cus : 16;
+  F.tile_envs = per_unit <= 2 || (per_unit <= 12 && weights <= static_cast<size_t>(C.D) * 24 * 1024) ? per_unit : 16;
   const int grid = (C.N + F.tile_envs - 1) / F.tile_envs;
   if (E.H <= 2 * 16 * kGenericWaves)
     return go(C.D <= 32 ? fused_generic_kernel<1, 2, true> : fused_generic_kernel<1, 2, false>, grid, kGenericThreads,

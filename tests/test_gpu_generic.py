@@ -45,3 +45,21 @@ def test_generic_schedule_matches_oracle(D, N, H, K, T, batched):
     assert D == 1 or np.abs(traj["qty"]).sum() > 0
     if batched:
         batch.close()
+
+
+# Around the rule for environments per workgroup: weights of up to and past 24 KB a stock at three
+# environments for every compute unit, two for every one, and past twelve.
+@pytest.mark.parametrize("D,N,H,K", [(8, 600, 128, 2), (8, 600, 256, 2), (8, 500, 256, 2), (8, 3100, 64, 1)])
+def test_generic_schedule_environments_per_workgroup(D, N, H, K):
+    from paper_2501_10709_amd.vecenv import Ensemble, VecEnv
+    dev = cuda()
+    S, T = 7 * D + 1, 4
+    cfg, m = env_case(N, D, 5, T, 78)
+    acfg, actors, packed = actors_case(K, S, H, D)
+    ens = Ensemble(packed, K, S, H, D, dtype="bf16", max_batch=N, device=dev)
+    env = VecEnv(cfg, m.close, m.ind, device=dev)
+    obs0 = _np(env.reset())
+    traj = {k: _np(v) for k, v in env.rollout(T, ens=ens, sigma=0.1, noise_key=7, path="fused").items()}
+    check_replay(cfg, m, traj, obs0)
+    check_actions(actors, "bf16", traj, obs0, 0.1, 7, TOL_BF16)
+    assert np.abs(traj["qty"]).sum() > 0
