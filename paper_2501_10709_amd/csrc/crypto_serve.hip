@@ -17,9 +17,11 @@
 //
 // Bound by the latency of a tick: one MLP wavefront per SIMD (a wavefront's slice of W2 is 160
 // registers), so the layers run as stages fenced against reordering, each stage's products beside
-// the activations of the one before.  A tick of a 64-environment tile with five agents: 11.5 k
-// cycles (layer 1 2.9 k, layer 2 and 3 6 k, softmax 1.4 k, trade 1.9 k), 4.8 us from 6.7 with the
-// layers in the compiler's order and the market row waited for inside layer 1.
+// the activations of the one before.  A mix of 24 requests of up to 4096 environments and ticks, five
+// agents, 64-environment tiles: 18.6 ms, 4.5 us a tick of its longest chain of tiles (27.3 ms and 6.6 with
+// the layers in the compiler's order and the market row waited for inside layer 1).  In a build with
+// clock stamps, which keep the phases apart, a tick is 13.0 k cycles: layer 1 2.3 k, layers 2 and 3 6.4 k,
+// softmax 1.2 k, trade 1.9 k, the rest waits at the barriers.
 //
 // Scheduler.  Host-side: a FIFO queue, a first-fit allocator over the caller's device pool, the
 // active set, and per-chunk lists of (request, tile) items copied from pinned staging.
@@ -248,9 +250,10 @@ __global__ __launch_bounds__(kNT, 1) void crypto_chunk_kernel(ChunkArgs a) {
     for (int s = 0; s < nt; ++s) {
       const int64_t t = t0 + s;
       // Next tick's market row (the environment wavefront): requested during layer 1 and put into LDS
-      // there, or, where the layers are long enough to cover its way from memory, during layer 2
-      // (24 requests of five agents in 64-environment tiles 7.3 ms against 8.0 with it in layer 1; the
-      // smaller tiles are 5 to 15% slower with it in layer 2).
+      // there, or, where the layers are long enough to cover its way from memory, during layer 2 (the mix
+      // of 24 requests above 18.6 ms against 20.7 with it in layer 1; 24 requests of 64 environments and
+      // 400 ticks, three agents in 64-environment tiles 1.72 ms against 1.90, but five agents in
+      // 16-environment tiles 1.50 against 1.40 and one agent 2 to 5% slower).
       constexpr bool kStageLate = R * K >= 12;
       const auto stage_row = [&](double mid, const float4 (&f)[4]) {
         sp1[ce] = mid;

@@ -977,7 +977,9 @@ __host__ __device__ inline int generic_areas(int MR, const EnvConst& C, const En
 // stocks, 128 units and three actors a step takes 9.7 us, against 21.1 with a layer of one actor
 // at a time, four wavefronts and the chain by phases; 24 uneven groups up to 4096 environments and
 // 400 days at 256 units 25.9 ms against 42.7.
-// KM: actors of a pass at most.
+// KM: actors of a pass at most.  Registers set the limit: at 256 a lane (two wavefronts per SIMD) the
+// batched kernels still spill 57 of them on 16-row tiles and 237 on 32-row ones, 30 and 62 with KM = 2, and
+// the kernels for more than 256 units 44 to 55.
 template <int ROWT, int TMAX, bool ROWS, int KM = kPass>
 __device__ __forceinline__ void generic_tile(const EnvConst& C, const EnvState& st, const EnsDev& E,
                                              const FusedArgs& F, int tile, unsigned char* smem) {

@@ -20,10 +20,11 @@
 //
 // Bound by vector instruction issue: there is one wavefront per SIMD (the weights fill the register
 // file), and a step of 32 environments is 192 tanh a lane at about 50 cycles each, beside 3.8 k
-// cycles of matrix products, then the trade, a chain of dependent float64 steps.  Clock stamps of a
-// step: layer 1 6.1 k cycles, layer 2 14.6 k (3 k of it the trajectory stores), layer 3 1.4 k, the
-// trade 12 k, waits 2.5 k.  Per step of D = 30 with states, actions and rewards stored: 13.1 us at
-// N = 8192 (streamed schedule 20.7, resident 22.6), 7.6 us at N = 4096 (17.0, 11.6).
+// cycles of matrix products, then the trade, a chain of dependent float64 steps.  In a build with clock
+// stamps, which keep the phases apart, a step of 32 environments is 35.7 k cycles (16.1 us there): layer
+// 1 5.8 k, layer 2 14.0 k, layer 3 1.5 k, the trade 11.9 k (half of it the buys), waits 2.6 k.  Without
+// them, per step of D = 30 with states, actions and rewards stored: 13.1 us at N = 8192 (streamed schedule
+// 20.7, resident 22.6), 7.6 us at N = 4096 (17.0, 11.6).
 #include <utility>
 
 #include "device_common.h"

@@ -234,7 +234,7 @@ __device__ __forceinline__ void sum_f32(const Gemm& g, int m0, int n0, int bm, i
 
 // A TM x TN tile of C per workgroup, eight wavefronts of BI x BJ blocks each.  Bound by instruction
 // issue: a wavefront's 24 products per (block column, 32 k) leave room for about three vector
-// instructions each, and the split (5.5 an element) and the sums (2 an element and 32 k) take most
+// instructions each, and the split (6.5 an element) and the sums (2 an element and 32 k) take most
 // of it.  One workgroup per compute unit (two wavefronts per SIMD), the operand tiles
 // double-buffered in LDS: while block k is multiplied, block k + 1 is split into the other buffer
 // from registers and block k + 2 is requested.  Tiles are 256 wide where C is (every row of A is

@@ -1,8 +1,8 @@
 // The trading chain of Section 3.1 run by a 16-lane row of a wavefront: lane j of the row owns
 // stocks j and j + 16 (at most 32 stocks); the serial cash recurrences (the sells' proceeds, the
 // buys, the value) run on terms broadcast along the row by DPP row broadcasts, in stock order, so
-// every lane of the row holds the same cash.  Used by the resident fused rollout and by the row
-// variant of the environment step.
+// every lane of the row holds the same cash.  Used by the row variant of the environment step and by the
+// fused rollouts' resident, wide and (up to 32 stocks) generic schedules.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -124,8 +124,8 @@ __device__ __forceinline__ void row_prefixes(const double (&start)[NQ], const do
 // next stock with a buy order whose one-share debit fits the cash buys its whole order or what the
 // cash allows.  Both forms are exact; an event costs about a third of a segment.
 // LEAVE: wavefronts without a candidate leave before the segment (agents that only buy are soon there:
-// 100 given days of 30 stocks and 2048 environments take 188 us against 221, of 32 and 8192 375 against 418).  The
-// generic schedules go without: the branch costs their batched form's registers up to 4%.
+// 100 given days of 30 stocks and 2048 environments take 188 us against 221, of 32 stocks and 8192 375
+// against 418).  The generic schedules go without: the branch costs their batched form up to 4%.
 template <int NQ, bool LEAVE = true>
 __device__ __forceinline__ void buy_all_seg4(double (&cash)[NQ], int (&kown)[NQ][2], int lane, const BuySet (&B)[NQ][2],
                                              double one_p) {

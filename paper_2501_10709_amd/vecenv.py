@@ -90,9 +90,12 @@ class VecEnv:
         B.env_set_step_kernel(self.handle, kernel, envs_per_wave)
 
     def set_fused_tuning(self, schedule=0, row_tiles=0, tile_envs=0):
-        """Fused-rollout tuning: schedule (0 by shape and size, 1 streamed, 2 generic, 3 resident),
-        MFMA row tiles per workgroup (1, 2; 0 by N) and environments per workgroup (0: fill the
-        compute units)."""
+        """Fused-rollout tuning: schedule (0 by shape and size: resident up to eight environments per
+        compute unit, its wide form beyond, else streamed, else generic; 1 streamed or generic, 2
+        generic, 3 resident at any size where the shape allows), the streamed schedule's MFMA row
+        tiles per workgroup (1, 2; 0 by N, and the wide form is taken only with 0) and the
+        environments per workgroup (resident <= 8, wide <= 32, streamed <= 16 row_tiles; 0: fill the
+        compute units; the generic schedule chooses its own)."""
         B.env_set_fused_tuning(self.handle, schedule, row_tiles, tile_envs)
 
     def reset(self, return_obs=True):
