@@ -363,7 +363,7 @@ __device__ __forceinline__ void pass_products(const PassLayer& P, int lane, floa
     if (g + s < P.kend) products(s, g + s);
 }
 
-// kp actors (1..KM) and tj tiles of the wavefront (0..TM).
+// kp actors (1..KM, KM 2 or 3) and tj tiles of the wavefront (0..TM).
 template <int ROWT, int TM, int KM>
 __device__ __forceinline__ void pass_layer(const PassLayer& P, int kp, int tj, int lane, floatx4 (&acc)[KM][ROWT][TM]) {
 #pragma unroll
@@ -375,9 +375,14 @@ __device__ __forceinline__ void pass_layer(const PassLayer& P, int kp, int tj, i
   static_for<TM>([&](auto ji) {
     constexpr int TJ = ji + 1, RING = TJ <= 2 ? 4 : 2;
     if (tj != TJ) return;
-    static_for<KM>([&](auto ki) {
-      if (kp == ki + 1) pass_products<ROWT, ki + 1, TJ, RING>(P, lane, acc);
-    });
+    if (kp == 1) {
+      pass_products<ROWT, 1, TJ, RING>(P, lane, acc);
+    } else if constexpr (KM == 2) {
+      pass_products<ROWT, 2, TJ, RING>(P, lane, acc);
+    } else {
+      if (kp == 2) pass_products<ROWT, 2, TJ, RING>(P, lane, acc);
+      else pass_products<ROWT, 3, TJ, RING>(P, lane, acc);
+    }
   });
 }
 
@@ -978,7 +983,7 @@ __host__ __device__ inline int generic_areas(int MR, const EnvConst& C, const En
 // at a time, four wavefronts and the chain by phases; 24 uneven groups up to 4096 environments and
 // 400 days at 256 units 25.9 ms against 42.7.
 // KM: actors of a pass at most.  Registers set the limit: at 256 a lane (two wavefronts per SIMD) the
-// batched kernels still spill 57 of them on 16-row tiles and 237 on 32-row ones, 30 and 62 with KM = 2, and
+// batched kernels still spill 57 of them on 16-row tiles and 235 on 32-row ones, 30 and 60 with KM = 2, and
 // the kernels for more than 256 units 44 to 55.
 template <int ROWT, int TMAX, bool ROWS, int KM = kPass>
 __device__ __forceinline__ void generic_tile(const EnvConst& C, const EnvState& st, const EnsDev& E,
@@ -995,7 +1000,7 @@ __device__ __forceinline__ void generic_tile(const EnvConst& C, const EnvState& 
   const bool split = F.mt != nullptr;
   const int kin1 = split ? E.ke_pad : E.S_pad;
   const int st0 = kin1 + 8, sth = E.H + 8;
-  const int areas = min(KM, generic_areas(MR, C, E, st0));
+  const int areas = KM < kPass ? KM : generic_areas(MR, C, E, st0);
 
   const int me = wave * (MR / kOwnerWaves) + lane, n = n0 + me;
   const bool owner = wave < kOwnerWaves && lane < MR / kOwnerWaves && me < M;
@@ -1539,8 +1544,8 @@ hipError_t launch_batched(int rows, int actors, int blocks, size_t lds, const vo
   hipLaunchKernelGGL(zero_counter_kernel, dim3(1), dim3(64), 0, stream, counter);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // Two actors a pass where no group has more: the form of three spills registers (237 of 32-row tiles
-  // against 62).  30 days of 2 x 4000 environments, 5 and 17 stocks and two actors of 64 units take
+  // Two actors a pass where no group has more: the form of three spills registers (235 of 32-row tiles
+  // against 60).  30 days of 2 x 4000 environments, 5 and 17 stocks and two actors of 64 units take
   // 383 us against 614, 8000 of 5 stocks and one actor 313 against 537; with three actors the third is a
   // pass of its own, and 24 uneven groups take 28.1 ms against 25.9.
   const auto go_batched = [&](auto kern) {
