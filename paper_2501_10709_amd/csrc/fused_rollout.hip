@@ -1110,7 +1110,7 @@ __device__ __forceinline__ void generic_tile(const EnvConst& C, const EnvState& 
         }
       row_sums(cash, pro[0]);
       row_sums(cash, pro[1]);
-      buy_all_seg4<ROWT, false>(cash, kown, lane, B, C.one_p);
+      buy_all_seg4<ROWT>(cash, kown, lane, B, C.one_p);
 #pragma unroll
       for (int q = 0; q < ROWT; ++q) {
         v_new[q] = cash[q];

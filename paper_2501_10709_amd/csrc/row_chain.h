@@ -125,8 +125,9 @@ __device__ __forceinline__ void row_prefixes(const double (&start)[NQ], const do
 // cash allows.  Both forms are exact; an event costs about a third of a segment.
 // LEAVE: wavefronts without a candidate leave before the segment (agents that only buy are soon there:
 // 100 given days of 30 stocks and 2048 environments take 188 us against 221, of 32 stocks and 8192 375
-// against 418).  The generic schedules go without: the branch costs their batched form up to 4%.
-template <int NQ, bool LEAVE = true>
+// against 418), in the row kernel and the resident schedule.  The others go without: the branch costs the
+// batched form up to 4% and the wide schedule 0.5%.
+template <int NQ, bool LEAVE = false>
 __device__ __forceinline__ void buy_all_seg4(double (&cash)[NQ], int (&kown)[NQ][2], int lane, const BuySet (&B)[NQ][2],
                                              double one_p) {
 #pragma clang fp contract(off)
@@ -265,7 +266,7 @@ __device__ __forceinline__ void buy_all_rows(double& cash, int (&kown)[2], int l
   double c[1] = {cash};
   int k[1][2] = {{kown[0], kown[1]}};
   const BuySet S[1][2] = {{B[0], B[1]}};
-  buy_all_seg4<1>(c, k, lane, S, one_p);
+  buy_all_seg4<1, true>(c, k, lane, S, one_p);
   cash = c[0];
   kown[0] = k[0][0];
   kown[1] = k[0][1];
