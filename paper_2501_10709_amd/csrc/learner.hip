@@ -50,20 +50,20 @@ struct Gemm {
   int ones_row;
 };
 
-// Float32 products on the bfloat16 matrix cores.  Every float32 x is the exact sum of three
-// bfloat16 values, hi = bf16(x), mid = bf16(x - hi), lo = x - hi - mid (24 bits in three times 8),
-// and x y is the sum of nine products, of which mid*lo, lo*mid and lo*lo are below 2^-25 |x y| and
-// left out.  The other six take 6 x 16 cycles of a SIMD's matrix core for a 16 x 16 x 32 block,
-// where v_mfma_f32_16x16x4 takes 8 x 32.  The matrix core rounds a
-// sum that starts from zero to nearest, but adds a non-zero accumulator with its lower bits cut
+// Float32 products on the bfloat16 matrix cores.  A float32 x is the sum of three bfloat16 values,
+// hi = bf16(x), mid = bf16(x - hi), lo = x - hi - mid (24 bits in three times 8), exact where lo is not
+// below the smallest bfloat16 (|x| of 2^-110 and more), and x y is the sum of nine products, of which
+// mid*lo, lo*mid and lo*lo are below 2^-25 |x y| and left out.  The other six take 6 x 16 cycles of a
+// SIMD's matrix core for a 16 x 16 x 32 block, where v_mfma_f32_16x16x4 takes 8 x 32.  The matrix core
+// rounds a sum that starts from zero to nearest, but adds a non-zero accumulator with its lower bits cut
 // off, towards minus infinity: a bias that is the same in every row and adds up over a gradient
 // (seven times the float32 form's error).  So 32 terms of hi*hi are summed from zero, those of the
 // five small products in a chain of their own (where what is cut off is 2^-8 of that), and both
 // are added to the running float32 sum by ordinary additions.
-// The split is exact down to 2^-110 (below, the low part would fall under the smallest bfloat16,
-// 2^-133), so operands are split at 2^16 times their value, which has every float32's 24 bits above
-// that, and the sums are taken back by 2^-32; neither rounds.  It takes 1% of the gradient of a
-// 2048 x 252 rollout (5.13 to 5.18 ms); without it gradients of 1e-36 were 2e-4 off, of 1e-37 2e-3.
+// Operands are split at 2^16 times their value, which has all bits of every float32 above the smallest
+// bfloat16 (2^-133), and the sums are taken back by 2^-32; neither rounds.  It takes 1 to 1.5% of the
+// gradient of a 2048 x 252 rollout (5.13 to 5.18 ms, 5.15 to 5.23 on another card); without it gradients
+// of 1e-36 were 2e-4 off, of 1e-37 2e-3.
 // An operand that is infinite, NaN or beyond 2^112, or a sum beyond 2^96, makes a sum infinite or NaN; a
 // wavefront that finds one sums its elements again in float32.
 constexpr float kUp = 0x1p16f, kDown = 0x1p-32f;
